@@ -182,22 +182,6 @@ __global__ __launch_bounds__(256) void k_jt_store(JoinArgs a) {
   }
 }
 
-// Appends (slot, row | flag, w) to the fix-up list: one atomic per wave.
-__device__ __forceinline__ void fix_append(const JoinArgs& a, bool want, int64_t slot, uint32_t rowf, uint32_t w) {
-  const uint64_t b = ballot(want);
-  if (!b) return;
-  const int leader = __ffsll((unsigned long long)b) - 1;
-  uint32_t base = 0;
-  if (lane_id() == leader) base = atomicAdd(&a.ds->jt_nfix, (uint32_t)popc(b));
-  base = __shfl(base, leader, WAVE);
-  if (!want) return;
-  const int64_t at = (int64_t)base + popc(b & lanemask_lt());
-  if (!in_bounds(a.ds, at, a.fix_cap)) return;
-  a.fix[3 * at + 0] = (uint32_t)slot;
-  a.fix[3 * at + 1] = rowf;
-  a.fix[3 * at + 2] = w;
-}
-
 // Pass 2.  A launch that holds its slot's launch word joins the kernel that
 // holds the kernel word: it writes the kernel's link, the latency, its own
 // kernel count (1) and kernel aggregates.  A launch that lost is a duplicate
@@ -208,9 +192,11 @@ template <int IT>
 __global__ __launch_bounds__(256) void k_jt_resolve(JoinArgs a) {
   __shared__ unsigned long long s_c[JC_N];
   __shared__ unsigned long long s_h[64];
+  __shared__ uint32_t s_nfix, s_fix0;
   const int tid = threadIdx.x;
   if (tid < JC_N) s_c[tid] = 0;
   if (tid < 64) s_h[tid] = 0;
+  if (tid == 0) s_nfix = 0;
   __syncthreads();
   const int64_t n = a.ds->nJ;
   if (n == 0) return;
@@ -253,6 +239,8 @@ __global__ __launch_bounds__(256) void k_jt_resolve(JoinArgs a) {
     t1[u] = a.te[kr];
     t2[u] = a.ts[joins ? row[u] : 0u];
   }
+  uint64_t fb[IT];    // the wave's lanes whose item u goes to the fix-up list
+  uint32_t nfix = 0;  // their number over the items
 #pragma unroll
   for (int u = 0; u < IT; ++u) {
     const bool kern = (key[u] & 1) != 0;
@@ -294,11 +282,31 @@ __global__ __launch_bounds__(256) void k_jt_resolve(JoinArgs a) {
         ++c[JC_UNM_K];
       }
     }
-    const bool dup = live && !kern && lw[u] != row[u];
-    const bool shared = live && kern && kw[u] != row[u];
-    fix_append(a, dup || shared, slot[u], row[u] | (dup ? FIX_DUP : 0u), lw[u]);
+    // a launch or kernel that lost its word
+    fb[u] = ballot(live && (kern ? kw[u] : lw[u]) != row[u]);
+    nfix += (uint32_t)popc(fb[u]);
   }
+  // The list's places are taken once per workgroup: with one atomic per wave
+  // and item on the one counter, a trace of graph replays (nearly every
+  // kernel shares its launch: 200k kernels) spent 42 us here instead of 9.
+  uint32_t fix0 = 0;
+  if (nfix && lane_id() == 0) fix0 = atomicAdd(&s_nfix, nfix);
   jt_flush(a, c, s_c, s_h);
+  if (s_nfix == 0) return;  // (jt_flush has a barrier; uniform)
+  if (tid == 0) s_fix0 = atomicAdd(&a.ds->jt_nfix, s_nfix);
+  __syncthreads();
+  if (nfix) {
+    int64_t at = (int64_t)s_fix0 + __shfl(fix0, 0, WAVE);
+#pragma unroll
+    for (int u = 0; u < IT; ++u) {
+      const int64_t p = at + popc(fb[u] & lanemask_lt());
+      at += popc(fb[u]);
+      if (!((fb[u] >> lane_id()) & 1) || !in_bounds(a.ds, p, a.fix_cap)) continue;
+      a.fix[3 * p + 0] = (uint32_t)slot[u];
+      a.fix[3 * p + 1] = row[u] | ((key[u] & 1) ? 0u : FIX_DUP);
+      a.fix[3 * p + 2] = lw[u];
+    }
+  }
 }
 
 constexpr int JT_FIX_BLOCKS = 256;
@@ -326,6 +334,15 @@ __global__ __launch_bounds__(256) void k_jt_dups(JoinArgs a) {
 // bin, kernel count and aggregates move); every kernel that shares a slot
 // joins the slot's final launch with atomics (or is unmatched) and adds its
 // times to the slot's edge extremes.
+//
+// A replayed graph's kernels all share one launch, and their entries follow
+// one another in the list: a kernel per lane put a thousand atomics on each
+// of its four words (408 us for 200k kernels, all but the first few
+// waiting for one another).  A wave therefore combines the lanes of its first
+// lane's launch and adds them once, FIX_ROUNDS launches per 64 entries; lanes
+// left over (a list in no order) add one by one, which is as good there.
+constexpr int FIX_ROUNDS = 4;
+
 __global__ __launch_bounds__(256) void k_jt_fix(JoinArgs a) {
   __shared__ unsigned long long s_c[JC_N];
   __shared__ unsigned long long s_h[64];
@@ -336,59 +353,80 @@ __global__ __launch_bounds__(256) void k_jt_fix(JoinArgs a) {
   const int64_t nf = min((int64_t)a.ds->jt_nfix, a.fix_cap);
   if ((int64_t)blockIdx.x * 256 >= nf) return;  // uniform: no entry for this workgroup
   int64_t c[JC_N] = {};
-  for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < nf; i += (int64_t)gridDim.x * 256) {
-    const uint32_t slot = a.fix[3 * i], rf = a.fix[3 * i + 1], w = a.fix[3 * i + 2];
-    const uint32_t row = rf & ~FIX_DUP;
-    const uint32_t l = a.L[slot];
-    if (rf & FIX_DUP) {
-      const uint32_t kr = a.K[slot];
-      if (l != row || kr == JT_EMPTY) continue;
-      // row < w: the kernel of the resolve pass moves from launch w to row
-      const int64_t o = a.off ? a.off[a.pid[row]] : 0;
-      const int64_t ks = a.ts[kr], ke = a.te[kr];
-      const int64_t x_old = ks - a.ts[w], x_new = ks - a.ts[row];
-      if (a.link) a.link[kr] = (int32_t)row;
-      if (a.aux) {
-        a.aux[w] = 0;
-        atomicAdd(&a.aux[row], 1);
-      }
-      atomicAdd(&s_h[lat_bin(x_old)], ~0ull);  // minus one
-      atomicAdd(&s_h[lat_bin(x_new)], 1ull);
-      c[JC_NEG] += (x_new < 0 ? 1 : 0) - (x_old < 0 ? 1 : 0);
-      if (a.contain) {
-        atomicMin((long long*)&a.lk_first[row], (long long)(ks - o));
-        atomicMax((long long*)&a.lk_last[row], (long long)(ke - o));
-        atomicAdd((unsigned long long*)&a.lk_sum[row], (unsigned long long)(ke - ks));
-      }
-      continue;
-    }
-    // a kernel that shares its slot
-    const int64_t o = a.off ? a.off[a.pid[row]] : 0;
-    const int64_t ks = a.ts[row], ke = a.te[row];
+  // n kernels of the slot (first start, last end and summed duration given) join launch l
+  auto join = [&](uint32_t l, uint32_t slot, int32_t n, int64_t first, int64_t last, int64_t sum) {
     if (a.kmax) {
-      atomicMax((long long*)&a.kmax[slot], (long long)(ke - o));
-      atomicMin((long long*)&a.kmin[slot], (long long)(ks - o));
+      atomicMax((long long*)&a.kmax[slot], (long long)last);
+      atomicMin((long long*)&a.kmin[slot], (long long)first);
     }
-    if (l == JT_EMPTY) {
-      if (a.link) a.link[row] = -1;
-      if (a.aux) a.aux[row] = -1;
-      ++c[JC_UNM_K];
-      continue;
-    }
-    if (a.link) a.link[row] = (int32_t)l;
-    if (a.aux) {
-      a.aux[row] = -1;
-      atomicAdd(&a.aux[l], 1);
-    }
-    ++c[JC_MATCHED];
-    const int64_t x = ks - a.ts[l];
-    if (x < 0) ++c[JC_NEG];
-    atomicAdd(&s_h[lat_bin(x)], 1ull);
+    if (l == JT_EMPTY) return;
+    if (a.aux) atomicAdd(&a.aux[l], n);
     if (a.contain) {
-      atomicMin((long long*)&a.lk_first[l], (long long)(ks - o));
-      atomicMax((long long*)&a.lk_last[l], (long long)(ke - o));
-      atomicAdd((unsigned long long*)&a.lk_sum[l], (unsigned long long)(ke - ks));
+      atomicMin((long long*)&a.lk_first[l], (long long)first);
+      atomicMax((long long*)&a.lk_last[l], (long long)last);
+      atomicAdd((unsigned long long*)&a.lk_sum[l], (unsigned long long)sum);
     }
+  };
+  for (int64_t i0 = (int64_t)blockIdx.x * 256; i0 < nf; i0 += (int64_t)gridDim.x * 256) {  // uniform over the workgroup
+    const int64_t i = i0 + tid;
+    bool shared = false;  // a kernel that shares its slot
+    uint32_t slot = 0, l = JT_EMPTY;
+    int64_t first = I64MAX, last = I64MIN, dur = 0;
+    if (i < nf) {
+      const uint32_t rf = a.fix[3 * i + 1], w = a.fix[3 * i + 2], row = rf & ~FIX_DUP;
+      slot = a.fix[3 * i];
+      l = a.L[slot];
+      shared = !(rf & FIX_DUP);
+      const uint32_t kr = shared ? row : a.K[slot];
+      if (shared || (l == row && kr != JT_EMPTY)) {
+        const int64_t o = a.off ? a.off[a.pid[row]] : 0;
+        const int64_t ks = a.ts[kr], ke = a.te[kr];
+        first = ks - o;
+        last = ke - o;
+        dur = ke - ks;
+        if (!shared) {
+          // row < w: the kernel of the resolve pass moves from launch w to row
+          const int64_t x_old = ks - a.ts[w], x_new = ks - a.ts[row];
+          if (a.link) a.link[kr] = (int32_t)row;
+          if (a.aux) {
+            a.aux[w] = 0;
+            atomicAdd(&a.aux[row], 1);
+          }
+          atomicAdd(&s_h[lat_bin(x_old)], ~0ull);  // minus one
+          atomicAdd(&s_h[lat_bin(x_new)], 1ull);
+          c[JC_NEG] += (x_new < 0 ? 1 : 0) - (x_old < 0 ? 1 : 0);
+          if (a.contain) {
+            atomicMin((long long*)&a.lk_first[row], (long long)first);
+            atomicMax((long long*)&a.lk_last[row], (long long)last);
+            atomicAdd((unsigned long long*)&a.lk_sum[row], (unsigned long long)dur);
+          }
+        } else if (l == JT_EMPTY) {
+          if (a.link) a.link[row] = -1;
+          if (a.aux) a.aux[row] = -1;
+          ++c[JC_UNM_K];
+        } else {
+          if (a.link) a.link[row] = (int32_t)l;
+          if (a.aux) a.aux[row] = -1;
+          ++c[JC_MATCHED];
+          const int64_t x = ks - a.ts[l];
+          if (x < 0) ++c[JC_NEG];
+          atomicAdd(&s_h[lat_bin(x)], 1ull);
+        }
+      }
+    }
+    bool left = shared;
+    uint64_t todo = ballot(left);
+    for (int rd = 0; rd < FIX_ROUNDS && todo; ++rd) {  // uniform over the wave
+      const int lead = __ffsll((unsigned long long)todo) - 1;
+      const bool mine = left && slot == shfl(slot, lead);
+      const uint64_t m = ballot(mine);
+      const int64_t f = wave_min_i64(mine ? first : I64MAX), e = wave_max_i64(mine ? last : I64MIN);
+      const int64_t sm = wave_sum_i64(mine ? dur : 0);
+      if (lane_id() == lead) join(l, slot, popc(m), f, e, sm);
+      left = left && !mine;
+      todo &= ~m;
+    }
+    if (left) join(l, slot, 1, first, last, dur);
   }
   jt_flush(a, c, s_c, s_h);
 }

@@ -782,6 +782,36 @@ def test_duplicates_and_shared_launches_at_scale(H, seed):
     assert g["counters"]["n_dup_launch_corr"] > 10_000
 
 
+@pytest.mark.parametrize("per", [2, 13, 63, 64, 65, 700])
+@pytest.mark.parametrize("order", ["grouped", "shuffled"])
+def test_replay_groups_joined_by_waves(H, per, order):
+    """Launches that own `per` kernels each (the fix-up combines a wave's
+    kernels of one launch, four launches per wave, and leaves the rest to
+    single atomics): group sizes around the wave's 64 lanes, kernels of one
+    group side by side and in no order, some groups without a launch, some
+    launches twice."""
+    rng = np.random.default_rng(9600 + per)
+    W, G = 40_000_000, max(6, 9000 // per)
+    rows = []
+    for i in range(G):
+        pid, t = i % 2, int(rng.integers(0, W - 200_000))
+        if i % 5 != 4:
+            for k in range(2 if i % 7 == 3 else 1):
+                rows.append((1, pid, 0, t + k, t + 500, i, 0))
+        for k in range(per):
+            ks = t + int(rng.integers(-50, 100_000))
+            rows.append((2, pid, k % 3, ks, ks + int(rng.integers(0, 900)), i, k % 4))
+        rows.append((0, pid, 0, t - 100, t + 120_000, 0, i % 4))
+    if order == "shuffled":
+        rows = [rows[i] for i in rng.permutation(len(rows))]
+    e = np.zeros(200, synth.EDGE_DTYPE)
+    for f in ("prod", "cons"):
+        e[f + "_corr"] = rng.integers(0, G + 3, 200)
+        e[f + "_pid"] = e[f + "_corr"] % 2
+    cols, p = _rows(rows, P=2, S=3, T=1, W=W, thr=1000, edges=e)
+    check(H, cols, p, f"groups of {per}, {order}")
+
+
 # --------------------------------------------------------------- optional outputs
 OUTPUT_SETS = {
     "batch set": ("name_count", "name_sum", "name_min", "name_max", "busy", "idle", "gap_pid", "gap_stream",
