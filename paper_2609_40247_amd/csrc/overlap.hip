@@ -14,8 +14,7 @@
 // group; for each sibling it finds the stretch of that sibling's events its
 // own events fall among (two wave searches), stages it in LDS and takes each
 // co-rank by a binary search there.  More streams or groups: every event
-// searches its sibling groups in memory.  The interval's length is added to
-// every active pair, to the classes present and to "any".
+// searches its process's groups in memory, and the matrix cores sum the pairs.
 #include "internal.hpp"
 
 namespace hx {
@@ -39,50 +38,6 @@ struct SweepArgs {
   int64_t* class_overlap;
   int64_t* any_busy;
 };
-
-__device__ __attribute__((always_inline)) inline void add_interval(const SweepArgs& a, uint64_t m, int64_t len, int pid, int pid0,
-                                             const uint64_t* cmask, unsigned long long* s_pair,
-                                             unsigned long long* s_cls) {
-  if (len <= 0 || m == 0) return;
-  const int S = a.S;
-  const bool local = pid == pid0;
-  int present[3];
-  for (int c = 0; c < 3; ++c) present[c] = (m & cmask[c]) != 0;
-  if (local) {
-    atomicAdd(&s_cls[12], (unsigned long long)len);
-    for (int c = 0; c < 3; ++c) {
-      if (!present[c]) continue;
-      atomicAdd(&s_cls[c], (unsigned long long)len);
-      for (int c2 = 0; c2 < 3; ++c2)
-        if (present[c2]) atomicAdd(&s_cls[3 + c * 3 + c2], (unsigned long long)len);
-    }
-  } else {
-    if (a.any_busy) atomicAdd((unsigned long long*)&a.any_busy[pid], (unsigned long long)len);
-    for (int c = 0; c < 3; ++c) {
-      if (!present[c]) continue;
-      if (a.class_busy) atomicAdd((unsigned long long*)&a.class_busy[pid * 3 + c], (unsigned long long)len);
-      if (a.class_overlap)
-        for (int c2 = 0; c2 < 3; ++c2)
-          if (present[c2])
-            atomicAdd((unsigned long long*)&a.class_overlap[(pid * 3 + c) * 3 + c2], (unsigned long long)len);
-    }
-  }
-  // separate loops for LDS and HBM, so that neither becomes a flat atomic
-  if (local) {
-    for (uint64_t mi = m; mi; mi &= mi - 1) {
-      const int i = __ffsll((unsigned long long)mi) - 1;
-      for (uint64_t mj = m; mj; mj &= mj - 1)
-        atomicAdd(&s_pair[i * S + __ffsll((unsigned long long)mj) - 1], (unsigned long long)len);
-    }
-  } else if (a.pair) {
-    for (uint64_t mi = m; mi; mi &= mi - 1) {
-      const int i = __ffsll((unsigned long long)mi) - 1;
-      for (uint64_t mj = m; mj; mj &= mj - 1)
-        atomicAdd((unsigned long long*)&a.pair[((int64_t)pid * S + i) * S + __ffsll((unsigned long long)mj) - 1],
-                  (unsigned long long)len);
-    }
-  }
-}
 
 // First event of every (pid, stream) group; entry P * S is the event count.
 // One wave per group boundary searches the events 64-ary: each round every
@@ -153,49 +108,6 @@ __device__ __forceinline__ void stage_keys(const uint64_t* __restrict__ src, int
       if (x < cnt) dst[x] = v[u];
     }
   }
-}
-
-// Active-stream mask and next event time after event i (key `key`) from
-// binary searches of its process's sibling groups in memory; the own stream
-// is active after a start (even index in its group).
-__device__ __forceinline__ void item_global(const SweepArgs& a, int64_t i, uint64_t key, uint64_t tmask,
-                                            uint64_t smask, int pshift, uint64_t* m_out, uint64_t* tn_out) {
-  const int S = a.S;
-  const int pid = (int)(key >> pshift);
-  const int st = (int)(key & smask);
-  const int32_t* off = a.seg_off + (int64_t)pid * S;
-  uint64_t m = 0, tn = ~0ull;
-#pragma unroll 1
-  for (int s = 0; s < S; ++s) {
-    if (s == st) continue;
-    const int32_t Lq = off[s], Rq = off[s + 1];
-    int32_t lo = Lq, len = Rq - Lq;
-    uint64_t nx = ~0ull;
-    while (len > 0) {
-      const int32_t half = len >> 1;
-      const uint64_t v = a.ev[lo + half];
-      if (v < key) {
-        lo += half + 1;
-        len -= half + 1;
-      } else {
-        nx = v;
-        len = half;
-      }
-    }
-    if ((lo - Lq) & 1) m |= 1ull << s;
-    if (lo < Rq) {
-      const uint64_t t2 = (nx >> a.sb) & tmask;
-      tn = t2 < tn ? t2 : tn;
-    }
-  }
-  const int32_t own_L = off[st], own_R = off[st + 1];
-  if (((i - own_L) & 1) == 0) m |= 1ull << st;
-  if (i + 1 < own_R) {
-    const uint64_t t2 = (a.ev[i + 1] >> a.sb) & tmask;
-    tn = t2 < tn ? t2 : tn;
-  }
-  *m_out = m;
-  *tn_out = tn;
 }
 
 // Per-mask interval sums T[m] of one process (s_mlen, 256 entries, zero
@@ -492,46 +404,200 @@ __global__ __launch_bounds__(SW_THREADS) void k_sweep_groups(SweepArgs a) {
   flush_masks(a, pid, s_mlen, s_sub, s_cls, cm);
 }
 
-// Any number of streams and groups: tiles by position (several groups and
-// processes in one), every item searching its siblings in memory, intervals
-// added to the pair matrix of the workgroup's first process in LDS (others
-// straight to the outputs).
-__global__ __launch_bounds__(SW_THREADS) void k_sweep_global(SweepArgs a) {
-  __shared__ unsigned long long s_pair[64 * 64];
-  __shared__ unsigned long long s_cls[13];  // class_busy[3], class_overlap[9], any
+// Any number of streams and groups.  A wave takes 64 consecutive events;
+// every lane searches the events of its process's streams in memory,
+// SM_SIB streams at a time (the reads of a step of all of them in flight
+// together, and neighbouring lanes' reads on the same lines).  Searching for
+// key + 1 treats the own stream like the others: the count of its events up
+// to and including this one is odd after a start.
+//
+// The pair sums are a product: with M the events x streams matrix of active
+// bits and l the intervals' lengths, pairs = M^T diag(l) M, so the matrix
+// cores sum them exactly: l in 7-bit digits, one 16 x 16 x 64 integer product
+// per digit, 64 events and pair of 16-stream blocks.  The classes present
+// and "any" are four more columns in a block of their own.  Adding each
+// interval to every active pair with LDS atomics instead took 607 us on a
+// trace of 4 processes, 16 streams and 195k events (about 80 atomics an
+// event, and only 48 workgroups of 4096 events); this takes 35.
+constexpr int SM_THREADS = 256;
+constexpr int SM_WAVES = SM_THREADS / WAVE;
+constexpr int SM_CHUNK = SM_WAVES * WAVE;       // events per workgroup and round
+constexpr int SM_SIB = 4;
+constexpr int SM_BLOCKS = 2048;
+constexpr int SM_DIGITS = 6;                   // lengths are at most 2^40
+constexpr int SM_TILES = HERSCHEL_MAX_STREAMS / 16 + 1;  // blocks of 16 streams, and the classes
+static_assert((1LL << (7 * SM_DIGITS)) > HERSCHEL_MAX_WINDOW, "digits hold the longest interval");
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// Orders the wave's LDS writes before its reads.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Bit `b` of 16 events' 16-bit masks as 16 bytes of 0 or 1 (w: the masks two
+// to a word).  Byte order within a word is events 0, 2, 1, 3: the digits are
+// stored in the same order.
+__device__ __forceinline__ v4i mask_bytes(const uint4 w0, const uint4 w1, int b) {
+  v4i r;
+  r[0] = (int)(((w0.x >> b) & 0x00010001u) | (((w0.y >> b) & 0x00010001u) << 8));
+  r[1] = (int)(((w0.z >> b) & 0x00010001u) | (((w0.w >> b) & 0x00010001u) << 8));
+  r[2] = (int)(((w1.x >> b) & 0x00010001u) | (((w1.y >> b) & 0x00010001u) << 8));
+  r[3] = (int)(((w1.z >> b) & 0x00010001u) | (((w1.w >> b) & 0x00010001u) << 8));
+  return r;
+}
+
+__global__ __launch_bounds__(SM_THREADS) void k_sweep_many(SweepArgs a) {
+  extern __shared__ unsigned long long s_pair[];  // [S * S] of the workgroup's first process
+  __shared__ unsigned long long s_cls[13];        // class_busy[3], class_overlap[9], any
+  __shared__ __align__(16) uint16_t s_mask[SM_WAVES][SM_TILES][WAVE];
+  __shared__ __align__(16) uint8_t s_dig[SM_WAVES][SM_DIGITS][WAVE];
   __shared__ uint64_t s_cmask[3];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = lane_id(), wv = tid / WAVE;
   const int32_t n = a.ds->nEv;
-  const int64_t base = (int64_t)blockIdx.x * SW_TILE;
-  if (base >= n) return;
-  const int S = a.S;
-  for (int i = tid; i < 64 * 64; i += SW_THREADS) s_pair[i] = 0;
+  const int64_t per = cdiv(cdiv((int64_t)n, (int64_t)gridDim.x), (int64_t)SM_CHUNK) * SM_CHUNK;
+  const int64_t lo_i = (int64_t)blockIdx.x * per, hi_i = min((int64_t)n, lo_i + per);
+  if (lo_i >= hi_i) return;
+  const int S = a.S, nt = (S + 15) / 16;  // block nt: the classes
+  for (int i = tid; i < S * S; i += SM_THREADS) s_pair[i] = 0;
   if (tid < 13) s_cls[tid] = 0;
-  class_masks(a, s_cmask);
+  if (tid < 3) {
+    uint64_t m = 0;
+    for (int s = 0; s < S; ++s)
+      if ((a.cls ? a.cls[s] : 0) == tid) m |= 1ull << s;
+    s_cmask[tid] = m;
+  }
   const uint64_t tmask = (1ull << a.wb1) - 1;
-  const uint64_t smask = (1ull << a.sb) - 1;
   const int pshift = a.wb1 + a.sb;
-  const int pid0 = (int)(a.ev[base] >> pshift);
+  const int pid0 = (int)(a.ev[lo_i] >> pshift);
   __syncthreads();
-  const uint64_t cm[3] = {s_cmask[0], s_cmask[1], s_cmask[2]};
-  for (int jt = 0; jt < SW_ITEMS; ++jt) {
-    const int64_t i = base + (int64_t)jt * SW_THREADS + tid;
-    if (i >= n) break;
-    const uint64_t key = a.ev[i];
-    uint64_t m, tn;
-    item_global(a, i, key, tmask, smask, pshift, &m, &tn);
-    if (m == 0 || tn == ~0ull) continue;
-    const int64_t len = (int64_t)tn - (int64_t)((key >> a.sb) & tmask);
-    if (len <= 0) continue;
-    add_interval(a, m, len, (int)(key >> pshift), pid0, cm, s_pair, s_cls);
+  const uint64_t cm0 = s_cmask[0], cm1 = s_cmask[1], cm2 = s_cmask[2];
+  for (int64_t base = lo_i + wv * WAVE; base < hi_i; base += SM_CHUNK) {  // uniform over the wave
+    const int64_t i = base + lane;
+    const uint64_t key = a.ev[i < hi_i ? i : hi_i - 1];
+    const int pid = (int)(key >> pshift);
+    const int32_t* off = a.seg_off + (int64_t)pid * S;
+    uint64_t m = 0, tn = ~0ull;  // active streams, the next event's time
+    for (int s0 = 0; s0 < S; s0 += SM_SIB) {
+      int32_t lo[SM_SIB], len[SM_SIB], L[SM_SIB], R[SM_SIB];
+#pragma unroll
+      for (int u = 0; u < SM_SIB; ++u) {
+        // past the last stream: an empty group
+        L[u] = off[min(s0 + u, S)];
+        R[u] = off[min(s0 + u + 1, S)];
+      }
+      int32_t top = 0;
+#pragma unroll
+      for (int u = 0; u < SM_SIB; ++u) {
+        lo[u] = L[u];
+        len[u] = R[u] - L[u];
+        top = max(top, len[u]);
+      }
+      // the last event at or before this one in the group, if any (the
+      // group's first otherwise); a group of one or none reads nothing new
+      for (; top > 1; top -= top >> 1) {
+        uint64_t v[SM_SIB];
+#pragma unroll
+        for (int u = 0; u < SM_SIB; ++u) v[u] = a.ev[min(lo[u] + (len[u] >> 1), n - 1)];
+#pragma unroll
+        for (int u = 0; u < SM_SIB; ++u) {
+          const int32_t half = len[u] >> 1;
+          lo[u] = v[u] <= key ? lo[u] + half : lo[u];
+          len[u] -= half;
+        }
+      }
+      uint64_t v[SM_SIB], w[SM_SIB];
+#pragma unroll
+      for (int u = 0; u < SM_SIB; ++u) {
+        v[u] = a.ev[min(lo[u], n - 1)];
+        w[u] = a.ev[min(lo[u] + 1, n - 1)];
+      }
+#pragma unroll
+      for (int u = 0; u < SM_SIB; ++u) {
+        const bool past = len[u] > 0 && v[u] <= key;  // the event at lo is not after this one
+        const int32_t p = lo[u] + (past ? 1 : 0);
+        if ((p - L[u]) & 1) m |= 1ull << (s0 + u);
+        const uint64_t t2 = ((past ? w[u] : v[u]) >> a.sb) & tmask;
+        if (p < R[u]) tn = t2 < tn ? t2 : tn;
+      }
+    }
+    const int64_t span = (int64_t)tn - (int64_t)((key >> a.sb) & tmask);
+    const int64_t len = i < hi_i && m != 0 && tn != ~0ull && span > 0 ? span : 0;
+    wave_sync();  // the last round's reads
+    for (int t = 0; t < nt; ++t) s_mask[wv][t][lane] = (uint16_t)(m >> (16 * t));
+    s_mask[wv][nt][lane] = (uint16_t)((m & cm0 ? 1 : 0) | (m & cm1 ? 2 : 0) | (m & cm2 ? 4 : 0) | 8);
+    // one process at a time (nearly always the wave's only one)
+    for (uint64_t todo = ballot(len > 0); todo;) {
+      const int pc = shfl(pid, __ffsll((unsigned long long)todo) - 1);
+      const bool mine = pid == pc;
+      todo &= ~ballot(mine);
+      wave_sync();  // the last process's reads
+      // events 0, 1, 2, 3 of four at bytes 0, 2, 1, 3
+      const int at = (lane & ~3) | ((lane & 1) << 1) | ((lane >> 1) & 1);
+#pragma unroll
+      for (int d = 0; d < SM_DIGITS; ++d) s_dig[wv][d][at] = mine ? (uint8_t)((len >> (7 * d)) & 127) : (uint8_t)0;
+      wave_sync();
+      const int col = lane & 15, k0 = (lane >> 4) * 16;
+      for (int ti = 0; ti <= nt; ++ti) {
+        for (int tj = ti; tj <= (ti == nt ? nt : nt - 1); ++tj) {
+          v4i acc[SM_DIGITS] = {};
+          const uint4* wi = reinterpret_cast<const uint4*>(&s_mask[wv][ti][k0]);
+          const uint4* wj = reinterpret_cast<const uint4*>(&s_mask[wv][tj][k0]);
+          const v4i bi = mask_bytes(wi[0], wi[1], col), bj = mask_bytes(wj[0], wj[1], col);
+#pragma unroll
+          for (int d = 0; d < SM_DIGITS; ++d) {
+            const uint4 q = *reinterpret_cast<const uint4*>(&s_dig[wv][d][k0]);
+            // 1 -> 0xff: the digit where the bit is set
+            const v4i x = {(int)(q.x & ((uint32_t)bi[0] * 255u)), (int)(q.y & ((uint32_t)bi[1] * 255u)),
+                           (int)(q.z & ((uint32_t)bi[2] * 255u)), (int)(q.w & ((uint32_t)bi[3] * 255u))};
+            acc[d] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x, bj, acc[d], 0, 0, 0);
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            unsigned long long sum = 0;
+#pragma unroll
+            for (int d = 0; d < SM_DIGITS; ++d) sum += (unsigned long long)(uint32_t)acc[d][e] << (7 * d);
+            if (!sum) continue;
+            const int row = (lane >> 4) * 4 + e;
+            if (ti == nt) {  // classes: row and col below 3; "any" is 3
+              const bool diag = row == col;
+              if (row < 3 && col < 3) {
+                const int g = 3 + row * 3 + col;
+                if (pc == pid0) {
+                  atomicAdd(&s_cls[g], sum);
+                  if (diag) atomicAdd(&s_cls[row], sum);
+                } else {
+                  if (a.class_overlap) atomicAdd((unsigned long long*)&a.class_overlap[pc * 9 + row * 3 + col], sum);
+                  if (diag && a.class_busy) atomicAdd((unsigned long long*)&a.class_busy[pc * 3 + row], sum);
+                }
+              } else if (row == 3 && col == 3) {
+                if (pc == pid0)
+                  atomicAdd(&s_cls[12], sum);
+                else if (a.any_busy)
+                  atomicAdd((unsigned long long*)&a.any_busy[pc], sum);
+              }
+              continue;
+            }
+            const int i = ti * 16 + row, j = tj * 16 + col;
+            if (i >= S || j >= S) continue;
+            if (pc == pid0) {
+              atomicAdd(&s_pair[i * S + j], sum);
+              if (ti != tj) atomicAdd(&s_pair[j * S + i], sum);
+            } else if (a.pair) {
+              unsigned long long* o = (unsigned long long*)a.pair + (int64_t)pc * S * S;
+              atomicAdd(&o[i * S + j], sum);
+              if (ti != tj) atomicAdd(&o[j * S + i], sum);
+            }
+          }
+        }
+      }
+    }
   }
   __syncthreads();
-  if (a.pair) {
-    for (int i = tid; i < S * S; i += SW_THREADS)
+  if (a.pair)
+    for (int i = tid; i < S * S; i += SM_THREADS)
       if (s_pair[i]) atomicAdd((unsigned long long*)&a.pair[(int64_t)pid0 * S * S + i], s_pair[i]);
-  }
-  if (a.class_busy && tid < 3 && s_cls[tid])
-    atomicAdd((unsigned long long*)&a.class_busy[pid0 * 3 + tid], s_cls[tid]);
+  if (a.class_busy && tid < 3 && s_cls[tid]) atomicAdd((unsigned long long*)&a.class_busy[pid0 * 3 + tid], s_cls[tid]);
   if (a.class_overlap && tid >= 3 && tid < 12 && s_cls[tid])
     atomicAdd((unsigned long long*)&a.class_overlap[pid0 * 9 + (tid - 3)], s_cls[tid]);
   if (a.any_busy && tid == 12 && s_cls[12]) atomicAdd((unsigned long long*)&a.any_busy[pid0], s_cls[12]);
@@ -558,8 +624,8 @@ void launch_overlap(Ctx& c) {
     // at most one partial tile per group beyond the full ones
     hipLaunchKernelGGL(k_sweep_groups, dim3((unsigned)(cdiv(c.ev_cap, SW_TILE) + G)), dim3(SW_THREADS), 0, c.st, a);
   } else {
-    hipLaunchKernelGGL(k_sweep_global, dim3((unsigned)std::max<int64_t>(cdiv(c.ev_cap, SW_TILE), 1)),
-                       dim3(SW_THREADS), 0, c.st, a);
+    const int64_t grid = std::min<int64_t>(std::max<int64_t>(cdiv(c.ev_cap, SM_CHUNK), 1), SM_BLOCKS);
+    hipLaunchKernelGGL(k_sweep_many, dim3((unsigned)grid), dim3(SM_THREADS), (size_t)c.S * c.S * 8, c.st, a);
   }
 }
 

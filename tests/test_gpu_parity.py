@@ -351,6 +351,20 @@ def test_64_streams_overlap(H):
     check(H, tr.columns(), p, "64 streams")
 
 
+@pytest.mark.parametrize("S", [9, 15, 16, 17, 33, 48, 64])
+@pytest.mark.parametrize("P,rows,window", [(1, 700, 1 << 40), (3, 9_000, 1 << 30), (300, 5_000, 40_000)])
+def test_overlap_beyond_8_streams(H, S, P, rows, window):
+    """Pair sums by blocks of 16 streams (edges of a block, one block and
+    several), lengths up to the longest window's 41 bits, one process, several
+    and many per wave of events, streams without kernels among them."""
+    tr = synth.random_small(9700 + S + P, n_rows=rows, window=window, n_procs=P, n_streams=S, corr_range=rows // 2,
+                            flags=2)
+    cols = tr.columns()
+    if P == 1:  # long runs on a few streams
+        cols["lane"] = np.where(cols["kind"] == 2, cols["lane"] // 4 * 4 % S, cols["lane"]).astype(np.int32)
+    check(H, cols, tr.params, f"{S} streams, {P} processes")
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_sparse_correlation_ids(H, seed):
     """The same traces with every correlation id spread by 2^30: no id table
