@@ -174,34 +174,6 @@ __device__ __forceinline__ uint64_t jt_hash(uint64_t key) {
   return x;
 }
 
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-  for (int d = 32; d >= 1; d >>= 1) v += shfl_down(v, d);
-  return shfl(v, 0);
-}
-__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
-  return (int64_t)wave_sum_u64((uint64_t)v);
-}
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-  for (int d = 32; d >= 1; d >>= 1) {
-    uint64_t o = shfl_down(v, d);
-    v = o > v ? o : v;
-  }
-  return shfl(v, 0);
-}
-__device__ __forceinline__ int64_t wave_min_i64(int64_t v) {
-  for (int d = 32; d >= 1; d >>= 1) {
-    int64_t o = shfl_down(v, d);
-    v = o < v ? o : v;
-  }
-  return shfl(v, 0);
-}
-__device__ __forceinline__ int64_t wave_max_i64(int64_t v) {
-  for (int d = 32; d >= 1; d >>= 1) {
-    int64_t o = shfl_down(v, d);
-    v = o > v ? o : v;
-  }
-  return shfl(v, 0);
-}
 // DPP (data-parallel primitives: a VALU move that reads another lane of the
 // same row) in its GFX9 forms.  A row is 16 lanes: row_shr:d moves lane
 // l - d of the row to lane l; row_bcast:15 carries lane 15 of each row to
@@ -227,46 +199,63 @@ __device__ __forceinline__ uint64_t dpp64(uint64_t old, uint64_t v) {
   return ((uint64_t)dpp32<CTRL, ROWS>((uint32_t)(old >> 32), (uint32_t)(v >> 32)) << 32) |
          dpp32<CTRL, ROWS>((uint32_t)old, (uint32_t)v);
 }
-// Inclusive prefix maximum over the wave (unsigned, identity 0): doubling
-// shifts inside each row, then each row takes the maxima of the rows
-// before it by the two broadcasts.
-__device__ __forceinline__ uint64_t wave_prefix_max_u64(uint64_t v) {
-  uint64_t o;
-  o = dpp64<DPP_ROW_SHR1>(0ull, v);
-  v = o > v ? o : v;
-  o = dpp64<DPP_ROW_SHR2>(0ull, v);
-  v = o > v ? o : v;
-  o = dpp64<DPP_ROW_SHR4>(0ull, v);
-  v = o > v ? o : v;
-  o = dpp64<DPP_ROW_SHR8>(0ull, v);
-  v = o > v ? o : v;
-  o = dpp64<DPP_ROW_BCAST15, 0xa>(0ull, v);
-  v = o > v ? o : v;
-  o = dpp64<DPP_ROW_BCAST31, 0xc>(0ull, v);
-  v = o > v ? o : v;
+// Inclusive scan over the wave in lane order: doubling shifts inside each
+// row, then each row takes the results of the rows before it by the two
+// broadcasts.  combine(older, newer) with `id` the identity on the left.
+// Twelve VALU moves and six combines, against twelve dependent trips through
+// the LDS crossbar with shuffles.
+template <class F>
+__device__ __forceinline__ uint64_t wave_scan_u64(uint64_t v, uint64_t id, F combine) {
+  v = combine(dpp64<DPP_ROW_SHR1>(id, v), v);
+  v = combine(dpp64<DPP_ROW_SHR2>(id, v), v);
+  v = combine(dpp64<DPP_ROW_SHR4>(id, v), v);
+  v = combine(dpp64<DPP_ROW_SHR8>(id, v), v);
+  v = combine(dpp64<DPP_ROW_BCAST15, 0xa>(id, v), v);
+  v = combine(dpp64<DPP_ROW_BCAST31, 0xc>(id, v), v);
   return v;
+}
+__device__ __forceinline__ uint64_t wave_prefix_max_u64(uint64_t v) {
+  return wave_scan_u64(v, 0ull, [](uint64_t o, uint64_t x) { return o > x ? o : x; });
+}
+__device__ __forceinline__ uint64_t wave_incl_sum(uint64_t v) {
+  return wave_scan_u64(v, 0ull, [](uint64_t o, uint64_t x) { return o + x; });
+}
+__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
+  v += dpp32<DPP_ROW_SHR1>(0u, v);
+  v += dpp32<DPP_ROW_SHR2>(0u, v);
+  v += dpp32<DPP_ROW_SHR4>(0u, v);
+  v += dpp32<DPP_ROW_SHR8>(0u, v);
+  v += dpp32<DPP_ROW_BCAST15, 0xa>(0u, v);
+  v += dpp32<DPP_ROW_BCAST31, 0xc>(0u, v);
+  return v;
+}
+// v of lane `l` (the same for the whole wave) in every lane.
+__device__ __forceinline__ uint32_t wave_read(uint32_t v, int l) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+__device__ __forceinline__ uint64_t wave_read(uint64_t v, int l) {
+  return ((uint64_t)wave_read((uint32_t)(v >> 32), l) << 32) | wave_read((uint32_t)v, l);
+}
+// Sums and extremes over the wave, in every lane.
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) { return wave_read(wave_incl_sum(v), WAVE - 1); }
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) { return wave_read(wave_incl_sum(v), WAVE - 1); }
+__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) { return (int64_t)wave_sum_u64((uint64_t)v); }
+__device__ __forceinline__ int64_t wave_min_i64(int64_t v) {
+  return (int64_t)wave_read(wave_scan_u64((uint64_t)v, (uint64_t)I64MAX,
+                                          [](uint64_t o, uint64_t x) { return (int64_t)o < (int64_t)x ? o : x; }),
+                            WAVE - 1);
+}
+__device__ __forceinline__ int64_t wave_max_i64(int64_t v) {
+  return (int64_t)wave_read(wave_scan_u64((uint64_t)v, (uint64_t)I64MIN,
+                                          [](uint64_t o, uint64_t x) { return (int64_t)o > (int64_t)x ? o : x; }),
+                            WAVE - 1);
 }
 // Lane l takes v of lane l - 1; lane 0 takes `fill`.
 __device__ __forceinline__ uint64_t wave_shift_up1_u64(uint64_t v, uint64_t fill) {
   return dpp64<DPP_WAVE_SHR1>(fill, v);
 }
 // Maximum over the wave (unsigned), in every lane.
-__device__ __forceinline__ uint64_t wave_allmax_u64(uint64_t v) {
-  v = wave_prefix_max_u64(v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, WAVE - 1);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), WAVE - 1);
-  return ((uint64_t)hi << 32) | lo;
-}
-
-// Inclusive prefix sum across the wave.
-__device__ __forceinline__ uint32_t wave_incl_sum_u32(uint32_t v) {
-  int l = lane_id();
-  for (int d = 1; d < WAVE; d <<= 1) {
-    uint32_t o = shfl_up(v, d);
-    if (l >= d) v += o;
-  }
-  return v;
-}
+__device__ __forceinline__ uint64_t wave_allmax_u64(uint64_t v) { return wave_read(wave_prefix_max_u64(v), WAVE - 1); }
 
 // --------------------------------------------------------- memory helpers
 __device__ __forceinline__ uint64_t ld_agent(const uint64_t* p) {
@@ -351,8 +340,11 @@ struct OpSegMax {
   }
   __device__ static uint32_t seg(uint64_t v) { return (uint32_t)(v >> 42); }
   __device__ static uint64_t m(uint64_t v) { return v & M_MASK; }
+  // 0 is the identity on both sides (as the newer part it also stands for
+  // zero-length elements of segment 0 after an older part of segment 0)
   __device__ static uint64_t combine(uint64_t older, uint64_t newer) {
     if (newer & HEAD) return newer;
+    if (newer == 0) return older;
     uint64_t a = older & M_MASK, b = newer & M_MASK;
     return (newer & ~(M_MASK | HEAD)) | (older & HEAD) | (a > b ? a : b);
   }
@@ -360,9 +352,11 @@ struct OpSegMax {
 };
 
 // Decoupled look-back executed by ONE whole wave.  Publishes the tile's
-// aggregate, combines the predecessors' values newest-first 64 at a time,
-// publishes the inclusive prefix and returns the exclusive prefix (all
-// lanes).  Tile 0 publishes its prefix directly.
+// aggregate, combines the predecessors' values 64 at a time (lane 63 the
+// newest), publishes the inclusive prefix and returns the exclusive prefix
+// (all lanes).  A window is complete once the newest prefix in it and
+// everything newer are there: older words need no wait.  Tile 0 publishes
+// its prefix directly.
 template <class Op>
 __device__ uint64_t wave_lookback(uint64_t* status, int tile, uint64_t agg, DevState* ds) {
   const int lane = lane_id();
@@ -376,10 +370,14 @@ __device__ uint64_t wave_lookback(uint64_t* status, int tile, uint64_t agg, DevS
   int pred = tile - 1;
   bool give_up = false;
   while (true) {
-    int idx = pred - lane;
+    const int idx = pred - (WAVE - 1) + lane;
     uint64_t s = idx >= 0 ? ld_agent(&status[idx]) : (LB_PRE | Op::identity());
-    uint64_t t0 = 0;
-    while (ballot((s >> 62) == 0)) {
+    uint64_t t0 = 0, pre_mask;
+    for (;;) {
+      pre_mask = ballot((s >> 62) == 2);
+      const uint64_t missing = ballot((s >> 62) == 0);
+      const int newest = 63 - __clzll((long long)pre_mask);  // -1 without a prefix
+      if ((missing >> (newest + 1 < WAVE ? newest + 1 : 0)) == 0 || newest == WAVE - 1) break;
       if ((s >> 62) == 0) s = ld_agent(&status[idx]);
       const uint64_t now = spin_clock();
       if (t0 == 0) t0 = now;
@@ -390,15 +388,10 @@ __device__ uint64_t wave_lookback(uint64_t* status, int tile, uint64_t agg, DevS
       __builtin_amdgcn_s_sleep(1);
     }
     if (give_up) break;
-    uint64_t pre_mask = ballot((s >> 62) == 2);
-    int last = pre_mask ? (__ffsll((unsigned long long)pre_mask) - 1) : (WAVE - 1);
-    // ordered fold over lanes 0..last, lane 0 newest: w = v[last] o ... o v[0]
-    uint64_t v = (lane <= last) ? (s & LB_VAL) : Op::identity();
-    for (int d = 1; d < WAVE; d <<= 1) {
-      uint64_t o = shfl_down(v, d);  // lane + d is older
-      if (lane + d <= last && (lane & ((d << 1) - 1)) == 0) v = Op::combine(o, v);
-    }
-    uint64_t w = shfl(v, 0);
+    const int first = pre_mask ? 63 - __clzll((long long)pre_mask) : 0;
+    const uint64_t v = lane >= first ? (s & LB_VAL) : Op::identity();
+    const uint64_t w = wave_read(
+        wave_scan_u64(v, Op::identity(), [](uint64_t o, uint64_t x) { return Op::combine(o, x); }), WAVE - 1);
     acc = have ? Op::combine(w, acc) : w;
     have = true;
     if (pre_mask) break;
@@ -422,26 +415,18 @@ __device__ __forceinline__ int take_ticket(DevState* ds, int slot, int* smem) {
 
 // ------------------------------------------------------------ block scans
 // Exclusive sum over a block of NT threads (NT a multiple of 64, <= 1024).
-template <int NT>
-__device__ uint32_t block_excl_sum(uint32_t v, uint32_t* scratch /* >= NT/64 + 1 */, uint32_t* total) {
-  const int lane = lane_id(), wv = threadIdx.x / WAVE;
-  uint32_t inc = wave_incl_sum_u32(v);
+// Every wave scans the waves' totals by itself.  `scratch` may be written
+// again only after another barrier.
+template <int NT, class T>
+__device__ __forceinline__ T block_excl_sum(T v, T* scratch /* NT / 64 */, T* total) {
+  constexpr int NW = NT / WAVE;
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const T inc = wave_incl_sum(v);
   if (lane == WAVE - 1) scratch[wv] = inc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t run = 0;
-    for (int w = 0; w < NT / WAVE; ++w) {
-      uint32_t t = scratch[w];
-      scratch[w] = run;
-      run += t;
-    }
-    scratch[NT / WAVE] = run;
-  }
-  __syncthreads();
-  uint32_t r = scratch[wv] + inc - v;
-  if (total) *total = scratch[NT / WAVE];
-  __syncthreads();
-  return r;
+  const T ws = wave_incl_sum(lane < NW ? scratch[lane] : (T)0);
+  if (total) *total = wave_read(ws, NW - 1);
+  return (wv > 0 ? wave_read(ws, wv - 1) : (T)0) + inc - v;
 }
 
 __device__ __forceinline__ int bits_of(uint64_t x) { return x == 0 ? 0 : 64 - __clzll((long long)x); }

@@ -96,7 +96,6 @@ constexpr int VB_ITEMS = CT_TILE / VB_THREADS;
 
 __global__ __launch_bounds__(VB_THREADS) void k_vbuild(ContainArgs a) {
   __shared__ uint64_t s_w[VB_THREADS / WAVE];
-  __shared__ uint64_t s_tmax;
   const int tid = threadIdx.x, lane = lane_id(), wv = tid / WAVE;
   const int64_t n = a.ds->nCL;
   const int par = (int)a.ds->sort_parity[1];
@@ -146,17 +145,14 @@ __global__ __launch_bounds__(VB_THREADS) void k_vbuild(ContainArgs a) {
   }
   if (lane == 0) s_w[wv] = wmax;
   __syncthreads();
-  if (tid == 0) {
-    uint64_t t = 0;
-    for (int w = 0; w < VB_THREADS / WAVE; ++w) t = s_w[w] > t ? s_w[w] : t;
-    s_tmax = t;
-    a.M[2][tile] = t;
-    for (int l = 3; l < a.nlev; ++l)
-      if (t) atomicMax((unsigned long long*)&a.M[l][tile >> (6 * (l - 2))], (unsigned long long)t);
-  }
-  __syncthreads();
   if (wv == 0) {
-    const uint64_t ex = wave_lookback<OpMax>(a.vb_status, tile, s_tmax, a.ds);
+    const uint64_t t = wave_allmax_u64(lane < VB_THREADS / WAVE ? s_w[lane] : 0ull);
+    if (lane == 0) {
+      a.M[2][tile] = t;
+      for (int l = 3; l < a.nlev; ++l)
+        if (t) atomicMax((unsigned long long*)&a.M[l][tile >> (6 * (l - 2))], (unsigned long long)t);
+    }
+    const uint64_t ex = wave_lookback<OpMax>(a.vb_status, tile, t, a.ds);
     if (lane == 0) a.pmt[tile] = ex;
   }
 }
@@ -478,7 +474,7 @@ __global__ __launch_bounds__(256) void k_depth(ContainArgs a) {
     const int64_t pe = n - 1;
     for (int64_t q = key_is_op(keys[pe]) ? pe : a.par[pe]; q >= 0 && in_range(a.ds, q, n); q = a.par[q]) init_op(q);
   }
-  const uint64_t w = wave_sum_u64(imp);
+  const uint32_t w = wave_sum_u32(imp);
   if (lane_id() == 0 && w) atomicAdd(&s_imp, (unsigned long long)w);
   __syncthreads();
   if (threadIdx.x == 0 && s_imp) atomicAdd((unsigned long long*)&a.cnt->n_improper_nesting, s_imp);

@@ -114,12 +114,12 @@ __device__ __forceinline__ int64_t jt_find(const JoinArgs& a, int32_t pid, int64
 
 // Adds each thread's counts (signed: the fix-up moves latencies between
 // bins) to the workgroup's and then to one of the accumulator copies.
-__device__ __forceinline__ void jt_flush(const JoinArgs& a, int64_t (&c)[JC_N], unsigned long long* s_c,
+__device__ __forceinline__ void jt_flush(const JoinArgs& a, int32_t (&c)[JC_N], unsigned long long* s_c,
                                          unsigned long long* s_h) {
 #pragma unroll
   for (int q = 0; q < JC_N; ++q) {
-    const uint64_t w = wave_sum_u64((uint64_t)c[q]);
-    if (lane_id() == 0 && w) atomicAdd(&s_c[q], (unsigned long long)w);
+    const int32_t w = (int32_t)wave_sum_u32((uint32_t)c[q]);
+    if (lane_id() == 0 && w) atomicAdd(&s_c[q], (unsigned long long)(int64_t)w);
   }
   __syncthreads();
   unsigned long long* acc = &a.ds->join_acc[blockIdx.x % JOIN_COPIES][0];
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(256) void k_jt_resolve(JoinArgs a) {
   const bool dense = a.ds->join_direct != 0;
   const int64_t cap = a.ds->jt_slots;
   const int64_t i0 = (int64_t)blockIdx.x * (256 * IT) + tid;
-  int64_t c[JC_N] = {};
+  int32_t c[JC_N] = {};
   // round 1: the entries
   uint64_t key[IT];
   uint32_t row[IT], hs[IT];
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(256) void k_jt_fix(JoinArgs a) {
   __syncthreads();
   const int64_t nf = min((int64_t)a.ds->jt_nfix, a.fix_cap);
   if ((int64_t)blockIdx.x * 256 >= nf) return;  // uniform: no entry for this workgroup
-  int64_t c[JC_N] = {};
+  int32_t c[JC_N] = {};
   // n kernels of the slot (first start, last end and summed duration given) join launch l
   auto join = [&](uint32_t l, uint32_t slot, int32_t n, int64_t first, int64_t last, int64_t sum) {
     if (a.kmax) {

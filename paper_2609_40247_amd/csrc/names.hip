@@ -104,7 +104,7 @@ __global__ __launch_bounds__(KO_THREADS) void k_kernel_ops(NamesArgs a) {
   const int64_t n = a.ds->nK;
   if (n == 0) return;
   const int64_t p0 = (int64_t)blockIdx.x * KO_THREADS * KO_ITEMS + threadIdx.x;
-  if (p0 >= n) return;
+  if (p0 - lane_id() >= n) return;  // whole waves only (the sum below takes every lane)
   uint32_t r[KO_ITEMS];
 #pragma unroll
   for (int u = 0; u < KO_ITEMS; ++u) {
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(KO_THREADS) void k_kernel_ops(NamesArgs a) {
     a.aux[r[u]] = op[u];
     if (op[u] < 0) ++unattr;
   }
-  const uint64_t w = wave_sum_u64(unattr);
+  const uint32_t w = wave_sum_u32(unattr);
   if (lane_id() == 0 && w) atomicAdd(&a.ds->join_acc[blockIdx.x % JOIN_COPIES][JC_UNATTR], (unsigned long long)w);
 }
 

@@ -222,28 +222,28 @@ __global__ __launch_bounds__(PREP_THREADS) void k_prep(PrepArgs a) {
       atomicOr(&s_jp, 1ull << tp);
     }
   }
-  const int nlists = a.waits ? PREP_LISTS : PREP_LISTS - 1;  // the op-name list only with its outputs
-  if (tid < nlists) {
-    uint32_t run = 0;
-    for (int j = 0; j < PREP_ITEMS; ++j)
-      for (int w = 0; w < PREP_THREADS / WAVE; ++w) {
-        s_off[j][w][tid] = run;
-        run += (uint32_t)popc(s_bal[j][w][tid]);
-      }
-    s_tot[tid] = run;
-  }
   if (tid == 0 && s_bad != ~0ull) atomicMin((unsigned long long*)&a.ds->first_invalid, s_bad);
+  const int nlists = a.waits ? PREP_LISTS : PREP_LISTS - 1;  // the op-name list only with its outputs
+  if (wv < nlists) {
+    // wave w: list w's place of every (item, wave), one a lane, then its look-back
+    static_assert(PREP_ITEMS * (PREP_THREADS / WAVE) == WAVE, "one lane per item and wave");
+    const int j = lane / (PREP_THREADS / WAVE), w = lane % (PREP_THREADS / WAVE);
+    const uint32_t c = (uint32_t)popc(s_bal[j][w][wv]);
+    const uint32_t inc = wave_incl_sum(c);
+    s_off[j][w][wv] = inc - c;
+    const uint32_t tot = wave_read(inc, WAVE - 1);
+    const uint64_t ex = wave_lookback<OpSum>(a.status + (int64_t)wv * a.n_tiles, tile, tot, a.ds);
+    if (lane == 0) {
+      s_tot[wv] = tot;
+      s_base[wv] = ex;
+    }
+  }
   __syncthreads();
   if (a.jt_range && tid < 2 * JT_PROCS && ((s_jp >> (tid >> 1)) & 1)) {
     unsigned long long* dst = (unsigned long long*)(tid & 1 ? &a.ds->jt_hi[tid >> 1] : &a.ds->jt_lo[tid >> 1]);
     atomicMax(dst, s_jr[tid]);
   }
   if (a.jt_range && tid == 0 && s_jp) atomicOr((unsigned long long*)&a.ds->jt_present, s_jp);
-  if (wv < nlists) {
-    const uint64_t ex = wave_lookback<OpSum>(a.status + (int64_t)wv * a.n_tiles, tile, s_tot[wv], a.ds);
-    if (lane == 0) s_base[wv] = ex;
-  }
-  __syncthreads();
   if (tile == a.n_tiles - 1 && tid == 0) {
     const int64_t nK = (int64_t)(s_base[0] + s_tot[0]);
     const int64_t nC = (int64_t)(s_base[1] + s_tot[1]);

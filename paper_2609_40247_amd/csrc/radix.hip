@@ -262,7 +262,7 @@ constexpr int PLAN_LOADS = 16;
 
 __global__ __launch_bounds__(PLAN_THREADS) void k_hist_plan(HistJobs jobs, DevState* ds) {
   __shared__ __align__(16) uint32_t s_part[PLAN_GROUPS][256];
-  __shared__ uint32_t s_scan[PLAN_THREADS / WAVE + 1];
+  __shared__ uint32_t s_scan[PLAN_THREADS / WAVE];
   const HistJob jb = jobs.j[blockIdx.y];
   const int d = blockIdx.x;
   if (d >= jb.nd) return;
@@ -351,7 +351,7 @@ void k_radix_pass(SortJobs jobs, DevState* ds) {
   __shared__ uint64_t s_key[RS_TILE];
   __shared__ uint32_t s_val[RS_TILE];
   __shared__ uint32_t s_local[256];
-  __shared__ uint32_t s_scan[NW + 1];
+  __shared__ uint32_t s_scan[NW];
   __shared__ uint32_t s_lb_sum[NSL][256];
   __shared__ uint8_t s_lb_state[NSL][256];
   static_assert(NW * 256 * 4 <= RS_TILE * 8, "per-wave counts must fit the key area");
@@ -509,7 +509,7 @@ void k_radix_pass(SortJobs jobs, DevState* ds) {
   // Threads 0..255 own one digit each: the digit's first tile position
   // (exclusive sum over digits), then each wave's (plus the exclusive sum
   // over waves), in the key area.
-  const uint32_t local_excl = block_excl_sum<RS_THREADS>(cnt, s_scan, nullptr);
+  const uint32_t local_excl = block_excl_sum<RS_THREADS>(cnt, s_scan, (uint32_t*)nullptr);
   if (tid < 256) {
     s_local[tid] = local_excl;
     uint32_t run = local_excl;

@@ -168,12 +168,10 @@ __device__ __forceinline__ void walk(const UnionArgs& a, const Elem* x, int nv, 
 __global__ __launch_bounds__(UN_THREADS) void k_union(UnionArgs a) {
   __shared__ int s_tile;
   __shared__ uint64_t s_wv[UN_THREADS / WAVE];
-  __shared__ int s_wh[UN_THREADS / WAVE];
   __shared__ uint64_t s_tile_excl;
   __shared__ int64_t s_busy[64];
   __shared__ int32_t s_seg0;
-  __shared__ uint32_t s_scan[UN_THREADS / WAVE + 1];
-  __shared__ uint32_t s_tot[2];
+  __shared__ uint64_t s_scan[UN_THREADS / WAVE];
   __shared__ uint64_t s_base[2];
   __shared__ uint64_t s_ev[2 * UN_TILE];  // the tile's coverage-run endpoints, in order
 
@@ -286,81 +284,47 @@ __global__ __launch_bounds__(UN_THREADS) void k_union(UnionArgs a) {
       if (j < nv) last_seg = x[j].seg;
     agg = OpSegMax::make((uint32_t)last_seg, head, m);
   }
-  // Ordered inclusive scan over the wave (valid threads form a prefix).
-  uint64_t inc = agg;
-  bool hv = has;
-  for (int d = 1; d < WAVE; d <<= 1) {
-    const uint64_t o = shfl_up(inc, d);
-    const int oh = shfl_up((int)hv, d);
-    if (lane >= d && oh) {
-      inc = hv ? OpSegMax::combine(o, inc) : o;
-      hv = true;
-    }
-  }
-  // every lane takes part in the shuffles; lane 0 discards the result
-  const uint64_t lane_excl = shfl_up(inc, 1);
-  const int prev_hv = shfl_up((int)hv, 1);
-  const bool lane_excl_has = lane > 0 && prev_hv;
-  if (lane == WAVE - 1) {
-    s_wv[wv] = inc;
-    s_wh[wv] = hv;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    uint64_t run = 0;
-    bool rh = false;
-    for (int w = 0; w < UN_THREADS / WAVE; ++w) {
-      const uint64_t t = s_wv[w];
-      const bool th = s_wh[w];
-      s_wv[w] = run;
-      s_wh[w] = rh;
-      if (th) {
-        run = rh ? OpSegMax::combine(run, t) : t;
-        rh = true;
-      }
-    }
-    s_tile_excl = run;  // tile aggregate (temporarily)
-  }
+  // Ordered scans over the wave, then over the waves, then the tiles before
+  // (threads with no element are the list's last: what they make of the scan
+  // reaches only threads that have none either)
+  auto seg_max = [](uint64_t o, uint64_t x) { return OpSegMax::combine(o, x); };
+  const uint64_t inc = wave_scan_u64(agg, 0ull, seg_max);
+  const uint64_t lane_excl = wave_shift_up1_u64(inc, 0ull);
+  if (lane == WAVE - 1) s_wv[wv] = inc;
   __syncthreads();
   if (wv == 0) {
-    const uint64_t ex = wave_lookback<OpSegMax>(a.status, tile, s_tile_excl, a.ds);
+    constexpr int NW = UN_THREADS / WAVE;
+    const uint64_t ws = wave_scan_u64(lane < NW ? s_wv[lane] : 0ull, 0ull, seg_max);
+    const uint64_t we = wave_shift_up1_u64(ws, 0ull);
+    if (lane < NW) s_wv[lane] = we;
+    const uint64_t ex = wave_lookback<OpSegMax>(a.status, tile, wave_read(ws, NW - 1), a.ds);
     if (lane == 0) s_tile_excl = ex;
   }
   __syncthreads();
-  // Exclusive prefix for this thread: tile prefix, then waves, then lanes.
-  uint64_t pre = s_tile_excl;
-  bool pre_has = tile > 0;
-  if (s_wh[wv]) {
-    pre = pre_has ? OpSegMax::combine(pre, s_wv[wv]) : s_wv[wv];
-    pre_has = true;
-  }
-  if (lane_excl_has) {
-    pre = pre_has ? OpSegMax::combine(pre, lane_excl) : lane_excl;
-    pre_has = true;
-  }
-  const uint64_t m_in = (has && pre_has && (int32_t)OpSegMax::seg(pre) == x[0].seg) ? OpSegMax::m(pre) : 0;
+  // exclusive prefix for this thread: tile prefix, then waves, then lanes
+  const uint64_t pre = seg_max(seg_max(s_tile_excl, s_wv[wv]), lane_excl);
+  const uint64_t m_in = (has && (int32_t)OpSegMax::seg(pre) == x[0].seg) ? OpSegMax::m(pre) : 0;
 
   uint32_t ngap = 0, nev = 0;
   if (has) walk<0>(a, x, nv, prev_seg, next_seg, m_in, i0, nK, &ngap, &nev, 0, 0, s_busy, s_seg0, s_ev);
-  uint32_t gtot, etot;
-  const uint32_t gex = block_excl_sum<UN_THREADS>(ngap, s_scan, &gtot);
-  const uint32_t eex = block_excl_sum<UN_THREADS>(nev, s_scan, &etot);
-  if (tid == 0) {
-    s_tot[0] = gtot;
-    s_tot[1] = etot;
-  }
-  __syncthreads();
+  // gaps and endpoints before this thread's, in one scan (both counts of a
+  // tile stay below 2^32)
+  uint64_t tot;
+  const uint64_t before = block_excl_sum<UN_THREADS>(((uint64_t)ngap << 32) | nev, s_scan, &tot);
+  const uint32_t gex = (uint32_t)(before >> 32), eex = (uint32_t)before;
+  const uint32_t gtot = (uint32_t)(tot >> 32), etot = (uint32_t)tot;
   if (wv < 2) {
-    const uint64_t ex = wave_lookback<OpSum>(a.status + (int64_t)(1 + wv) * a.tiles_max, tile, s_tot[wv], a.ds);
+    const uint64_t ex =
+        wave_lookback<OpSum>(a.status + (int64_t)(1 + wv) * a.tiles_max, tile, wv == 0 ? gtot : etot, a.ds);
     if (lane == 0) s_base[wv] = ex;
   }
   if (tid < 64 && s_busy[tid]) atomicAdd((unsigned long long*)&a.busy[s_seg0 + tid], (unsigned long long)s_busy[tid]);
   __syncthreads();
   if (tile == ntiles - 1 && tid == 0) {
-    const int64_t g = (int64_t)(s_base[0] + s_tot[0]);
+    const int64_t g = (int64_t)(s_base[0] + gtot);
     *a.gaps_out = g;
     if (a.cnt) a.cnt->n_gaps_total = g;
-    *a.ev_out = (int32_t)(s_base[1] + s_tot[1]);
+    *a.ev_out = (int32_t)(s_base[1] + etot);
   }
   if (has && (ngap || nev)) {
     uint32_t g2, e2;
@@ -368,7 +332,7 @@ __global__ __launch_bounds__(UN_THREADS) void k_union(UnionArgs a) {
             s_ev);
   }
   __syncthreads();
-  const uint32_t ne = s_tot[1];
+  const uint32_t ne = etot;
   const int64_t eb = (int64_t)s_base[1];
   for (uint32_t i = tid; i < ne; i += UN_THREADS)
     if (in_range(a.ds, eb + i, a.ev_cap)) a.ev_keys[eb + i] = s_ev[i];

@@ -37,16 +37,6 @@ struct WaitsArgs {
   int64_t* op_idle;
 };
 
-// Inclusive sum over the wave.
-__device__ __forceinline__ uint64_t wave_incl_sum_u64(uint64_t v) {
-  const int l = lane_id();
-  for (int d = 1; d < WAVE; d <<= 1) {
-    const uint64_t o = shfl_up(v, d);
-    if (l >= d) v += o;
-  }
-  return v;
-}
-
 // Exclusive prefix sums of the idle intervals' lengths: a tile of DG_TILE
 // intervals per workgroup (consecutive per thread), a block scan, and the
 // tiles chained by a decoupled look-back (tiles by workgroup index); and each
@@ -70,25 +60,14 @@ __global__ __launch_bounds__(DG_THREADS) void k_dg_scan(WaitsArgs a) {
     len[j] = i < cnt ? l : 0;
     sum += len[j];
   }
-  const uint64_t inc = wave_incl_sum_u64(sum);
-  if (lane == WAVE - 1) s_w[wv] = inc;
-  __syncthreads();
-  if (tid == 0) {
-    uint64_t run = 0;
-    for (int w = 0; w < DG_THREADS / WAVE; ++w) {
-      const uint64_t t = s_w[w];
-      s_w[w] = run;
-      run += t;
-    }
-    s_base = run;  // the tile's total, for the look-back
-  }
-  __syncthreads();
+  uint64_t tot;
+  const uint64_t ex = block_excl_sum<DG_THREADS>(sum, s_w, &tot);
   if (wv == 0) {
-    const uint64_t ex = wave_lookback<OpSum>(a.dg_status, tile, s_base, a.ds);
-    if (lane == 0) s_base = ex;
+    const uint64_t before = wave_lookback<OpSum>(a.dg_status, tile, tot, a.ds);
+    if (lane == 0) s_base = before;
   }
   __syncthreads();
-  uint64_t pre = s_base + s_w[wv] + inc - sum;
+  uint64_t pre = s_base + ex;
 #pragma unroll
   for (int j = 0; j < DG_ITEMS; ++j) {
     const int64_t i = i0 + j;
