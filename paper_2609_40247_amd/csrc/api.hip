@@ -66,18 +66,22 @@ size_t layout_workspace(Ctx& c, char* base) {
   // region cleared by the init kernel
   c.zero_begin = base ? base + b.off : nullptr;
   const size_t z0 = b.off;
-  c.prep_tiles = cdiv(c.n, prep_tile_rows());
-  c.prep_status = b.take<uint64_t>(4 * std::max<int64_t>(c.prep_tiles, 1));
-  c.union_tiles = std::max<int64_t>(cdiv(n, union_tile_elems()), 1);
-  c.union_status = b.take<uint64_t>(3 * c.union_tiles);
+  // small windows have smaller tiles: room for them at any size, so that a
+  // workspace for n rows also serves every call with fewer
+  const int64_t nsm = std::min(n, SMALL_ROWS);
+  auto most = [&](int64_t (*rows)(bool)) { return std::max(cdiv(n, rows(false)), cdiv(nsm, rows(true))); };
+  c.prep_tiles = cdiv(c.n, prep_tile_rows(c.small));
+  c.prep_status = b.take<uint64_t>(4 * most(prep_tile_rows));
+  c.union_tiles = cdiv(n, union_tile_elems(c.small));
+  c.union_status = b.take<uint64_t>(3 * most(union_tile_elems));
   // key widths (also reported by herschel_sort_stats)
   sort_plan(c.sK, SORT_K, n, c.pb + c.sb + c.wb, true);
   sort_plan(c.sC, SORT_C, n, c.pb + c.tb + c.wb + 1, true);
   if (c.waits) {
     sort_plan(c.sD, SORT_D, n, c.pb + c.wb, true);
     sort_plan(c.sO, SORT_O, n, c.pb + c.nob + c.wb, true);
-    c.union_status_d = b.take<uint64_t>(3 * c.union_tiles);
-    c.union_status_o = b.take<uint64_t>(3 * c.union_tiles);
+    c.union_status_d = b.take<uint64_t>(3 * most(union_tile_elems));
+    c.union_status_o = b.take<uint64_t>(3 * most(union_tile_elems));
     c.dg_cap = n + c.P;  // idle intervals: at most one more per process than kernels
     c.dg_tiles = std::max<int64_t>(cdiv(c.dg_cap, 4096), 1);
     c.dg_status = b.take<uint64_t>(c.dg_tiles);
@@ -111,7 +115,10 @@ size_t layout_workspace(Ctx& c, char* base) {
     s->status0 = b.take<uint32_t>(s->tiles_max * RS_LB_WORDS);
     s->status1 = b.take<uint32_t>((int64_t)std::max(s->nd - 1, 1) * s->tiles_max * RS_LB_WORDS);
   }
-  c.hist_part = b.take<uint32_t>((int64_t)N_SORTS * HIST_MAX_BLOCKS * 8 * 256);
+  // (a workgroup's table per HIST_CHUNK keys; small windows keep their tiles' samples here)
+  c.hist_blocks = hist_blocks(n);
+  c.hist_part = b.take<uint32_t>((int64_t)N_SORTS * std::max<int64_t>((int64_t)c.hist_blocks * 8 * 256,
+                                                                     cdiv(std::min(n, TS_ROWS), TS_TILE) * WAVE * 2));
   c.k_rows = b.take<uint32_t>(n);
   // the join: prep's list, the correlation table (two slots per row bound
   // every dense id range it accepts; hashed slots use the power of two
@@ -215,6 +222,15 @@ static int crit_walk_max() {
   return v < 0 ? 0 : v > (1L << 20) ? (1 << 20) : (int)v;
 }
 
+// Stage timing for benchmarks (herschel_time_stage).
+static int g_stage = -1;
+static hipEvent_t g_ev0 = nullptr, g_ev1 = nullptr;
+// Windows whose kernels are launched level by level: up to SMALL_ROWS rows,
+// unless a stage is being timed.
+static bool small_window(int64_t n) {
+  return g_stage < 0 && n <= SMALL_ROWS;
+}
+
 // ------------------------------------------------------------- the call
 static int check_and_plan(Ctx& c, const herschel_events* ev, int64_t n, const herschel_params* p,
                           const herschel_outputs* out) {
@@ -271,6 +287,7 @@ static int check_and_plan(Ctx& c, const herschel_events* ev, int64_t n, const he
   c.T = p->n_threads;
   c.NN = p->n_names;
   c.NOP = p->n_op_names;
+  c.small = small_window(n);
   c.contain = contain;
   c.overlap = overlap;
   c.waits = (p->flags & HERSCHEL_OUT_WAITS) != 0;
@@ -289,9 +306,6 @@ static int check_and_plan(Ctx& c, const herschel_events* ev, int64_t n, const he
   return HERSCHEL_OK;
 }
 
-// Stage timing for benchmarks (herschel_time_stage).
-static int g_stage = -1;
-static hipEvent_t g_ev0 = nullptr, g_ev1 = nullptr;
 static inline void stage_begin(Ctx& c, int s) {
   if (s == g_stage && g_ev0) (void)hipEventRecord(g_ev0, c.st);
 }
@@ -357,14 +371,6 @@ static int enqueue_locked(Ctx& c, DeviceStreams* dsx) {
   auto wait = [&](hipStream_t s, int e) {
     if (!serial) (void)hipStreamWaitEvent(s, dsx->e[e], 0);
   };
-  stage_begin(c, HERSCHEL_STAGE_INIT);
-  launch_init(c);
-  stage_end(c, HERSCHEL_STAGE_INIT);
-  stage_begin(c, HERSCHEL_STAGE_PREP);
-  launch_prep(c);
-  if (c.crit) launch_crit_elist(c);  // the kernel-end list joins the sorts
-  stage_end(c, HERSCHEL_STAGE_PREP);
-
   // The timeline and containment sorts share their digit passes, pass p of
   // a sort being its digit first + p (a sort whose digit is skipped has no
   // tiles in the launch); both leave their lowest digit to the refine pass.
@@ -393,6 +399,31 @@ static int enqueue_locked(Ctx& c, DeviceStreams* dsx) {
   }
   int p_shared = 0;
   for (int i = 0; i < ks; ++i) p_shared = std::max(p_shared, ss[i]->nd - ss[i]->first);
+
+  if (c.small) {
+    launch_levels(c, ss, cc, ks, p_shared);
+    if (c.waits) {
+      launch_dg_scan(c);
+      launch_waits(c);
+    }
+    if (c.sol) launch_sol(c);
+    if (c.crit) {
+      launch_crit_kernels(c);
+      launch_crit_front(c);
+      launch_crit(c);
+    }
+    if (c.graph) launch_graph(c);
+    launch_finalize(c);
+    return hipGetLastError() == hipSuccess ? HERSCHEL_OK : HERSCHEL_EDEVICE;
+  }
+
+  stage_begin(c, HERSCHEL_STAGE_INIT);
+  launch_init(c);
+  stage_end(c, HERSCHEL_STAGE_INIT);
+  stage_begin(c, HERSCHEL_STAGE_PREP);
+  launch_prep(c);
+  if (c.crit) launch_crit_elist(c);  // the kernel-end list joins the sorts
+  stage_end(c, HERSCHEL_STAGE_PREP);
   stage_begin(c, HERSCHEL_STAGE_HIST);
   launch_hist_multi(c, ss, cc, ks);
   stage_end(c, HERSCHEL_STAGE_HIST);
@@ -517,6 +548,7 @@ static DeviceStreams* enqueue_setup() {
   static bool lds_attr = false;
   if (!lds_attr) {
     names_set_lds_attr();
+    level_set_lds_attr();
     lds_attr = true;
   }
   return device_streams();
@@ -902,6 +934,7 @@ int herschel_trace_analyze_static(const herschel_events* ev, int64_t n, const he
     static bool lds_attr = false;
     if (!lds_attr) {
       names_set_lds_attr();
+      level_set_lds_attr();
       lds_attr = true;
     }
     code = enqueue_locked(c, nullptr);

@@ -62,6 +62,7 @@ struct Ctx {
   herschel_outputs o{};
   int64_t W0 = 0, W1 = 0, W = 0, thr = 0;
   int P = 0, S = 0, T = 0, NN = 0, NOP = 0;
+  bool small = false;  // launched level by level
   bool contain = false, overlap = false, waits = false, sol = false, crit = false, graph = false;
   int NG = 0;                          // graph nodes (graph replay separation)
   int nob = 0;                         // bits of an op name (idle coincidence)
@@ -96,7 +97,8 @@ struct Ctx {
   SortBufs sD, sO;                   // device lane, op names (idle coincidence)
   SortBufs sE;                       // kernel ends (critical path)
   uint32_t* k_rows = nullptr;        // [n] admitted kernels' rows in row order (per-name tables)
-  uint32_t* hist_part = nullptr;     // [N_SORTS][HIST_MAX_BLOCKS][8 * 256] per-workgroup digit counts
+  int hist_blocks = 0;               // workgroup tables per sort in hist_part
+  uint32_t* hist_part = nullptr;     // [N_SORTS][hist_blocks][8 * 256] per-workgroup digit counts
   uint64_t* jkey = nullptr;          // [n] join list (prep): admitted launches and kernels in row order
   uint32_t* jrow = nullptr;          // [n] their rows
   uint32_t* jslot = nullptr;         // [n] their hashed slots
@@ -200,9 +202,12 @@ int graph_block_count(int64_t n_max, int NG);
 int sol_block_count(int64_t n_max, int NOP);
 bool sol_uses_tables(int NOP);
 
-int64_t prep_tile_rows();
-int64_t union_tile_elems();
+int64_t prep_tile_rows(bool small);
+int64_t union_tile_elems(bool small);
 void names_set_lds_attr();
+// small windows: everything up to the per-op aggregates, fused level by level
+void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks, int passes);
+void level_set_lds_attr();
 
 // digit histograms: keys per workgroup (at least), most workgroups per sort
 constexpr int HIST_CHUNK = 4096;
@@ -211,6 +216,19 @@ constexpr int HIST_MAX_BLOCKS = 256;
 // per-op aggregates: positions per workgroup, open ops kept per tile start
 constexpr int AG_TILE = 512;
 constexpr int AG_CHAIN = 64;
+
+// Small windows (up to SMALL_ROWS rows) are launched level by level on one
+// stream; beyond, the three chains after the sorts run side by side on three
+// streams (us a call, level by level against three streams, traces of 4
+// streams: 150k rows 152 / 190, 300k 164 / 171, 450k 183 / 195, 600k 214 /
+// 200).  The smallest (up to TS_ROWS, TS_TILES tiles) also have their lists
+// sorted tile by tile (60k rows 120 against 140 us; with more tiles the
+// merge's search per key and tile costs more than it saves where the rows
+// come in no order: 120k shuffled rows 215 against 158).
+constexpr int64_t SMALL_ROWS = 450000;
+constexpr int TS_TILE = 4096;
+constexpr int TS_TILES = 16;
+constexpr int64_t TS_ROWS = (int64_t)TS_TILE * TS_TILES;
 
 constexpr int RS_THREADS = 512;
 constexpr int RS_ITEMS = 8;

@@ -22,8 +22,8 @@
 namespace hx {
 
 constexpr int SW_THREADS = 512;
-constexpr int SW_ITEMS = 8;
-constexpr int SW_TILE = SW_THREADS * SW_ITEMS;
+// Events per thread: 8 in general, 2 for small windows (more tiles).
+constexpr int SW_ITEMS = 8, SW_ITEMS_SMALL = 2;
 constexpr int SW_SMAX = 8;     // most streams summed per active-stream mask
 constexpr int SB_CAP = 8192;   // sibling events staged in LDS per tile (64 KB)
 constexpr int SW_GROUPS = 256; // most (pid, stream) groups for group-aligned tiles
@@ -176,15 +176,16 @@ __device__ __forceinline__ void class_masks(const SweepArgs& a, uint64_t* s_cmas
 // a step issued together.  The sibling is active in the item's interval iff
 // the co-rank (cb - L + position) is odd, and the event at the position is
 // the sibling's next event.
+template <int ITEMS>
 __device__ __forceinline__ void sibling_search(const SweepArgs& a, const uint64_t* src, int32_t cnt, int32_t cb,
                                                int32_t L, int s2, const uint64_t* key, uint32_t valid, uint64_t& m8,
                                                uint64_t* tn) {
   if (!valid) return;
   const uint64_t tmask = (1ull << a.wb1) - 1;
   const int32_t cmax = cnt > 0 ? cnt - 1 : 0;
-  constexpr int HB = SW_ITEMS / 2;  // two halves, to bound the registers in flight
+  constexpr int HB = ITEMS / 2;  // two halves, to bound the registers in flight
 #pragma unroll
-  for (int hb = 0; hb < SW_ITEMS; hb += HB) {
+  for (int hb = 0; hb < ITEMS; hb += HB) {
     int32_t pos[HB];
 #pragma unroll
     for (int u = 0; u < HB; ++u) pos[u] = 0;
@@ -221,14 +222,15 @@ __device__ __forceinline__ void sibling_search(const SweepArgs& a, const uint64_
 // it (a branchless search in LDS) brackets its lower bound within k
 // positions, which a binary search in memory narrows.  Halves of the items
 // with none valid in the lane are skipped.
+template <int ITEMS>
 __device__ __forceinline__ void sibling_search_sampled(const SweepArgs& a, const uint64_t* samp, int32_t ns, int32_t k,
                                                        const uint64_t* src, int32_t cnt, int32_t cb, int32_t L, int s2,
                                                        const uint64_t* key, uint32_t valid, uint64_t& m8,
                                                        uint64_t* tn) {
   const uint64_t tmask = (1ull << a.wb1) - 1;
-  constexpr int HB = SW_ITEMS / 2;
+  constexpr int HB = ITEMS / 2;
 #pragma unroll
-  for (int hb = 0; hb < SW_ITEMS; hb += HB) {
+  for (int hb = 0; hb < ITEMS; hb += HB) {
     if (((valid >> hb) & ((1u << HB) - 1)) == 0) continue;
     int32_t idx[HB];
 #pragma unroll
@@ -278,7 +280,7 @@ __device__ __forceinline__ void sibling_search_sampled(const SweepArgs& a, const
   }
 }
 
-// Up to 8 streams and SW_GROUPS (pid, stream) groups: tiles of SW_TILE
+// Up to 8 streams and SW_GROUPS (pid, stream) groups: tiles of (SW_THREADS * ITEMS)
 // events inside one group, numbered group after group (each workgroup
 // finds its group from the groups' tile counts), items striped over the
 // workgroup so that neighbouring lanes hold neighbouring events.  For each
@@ -301,6 +303,7 @@ struct SweepGroupsLds {
   int32_t s_rng[2 * SW_SMAX];     // per sibling: its co-ranks of the tile's first and last events
 };
 
+template <int ITEMS>
 __device__ __forceinline__ void sweep_groups_body(const SweepArgs& a, SweepGroupsLds& lds, uint32_t bx) {
   auto& s_sib = lds.s_sib;
   auto& s_mlen = lds.s_mlen;
@@ -321,7 +324,7 @@ __device__ __forceinline__ void sweep_groups_body(const SweepArgs& a, SweepGroup
     int32_t run = 0;
     for (int g0 = 0; g0 <= G; g0 += WAVE) {  // uniform over the wave
       const int g = g0 + lane;
-      const int32_t c = g < G ? (int32_t)cdiv((int64_t)(s_goff[g + 1] - s_goff[g]), (int64_t)SW_TILE) : 0;
+      const int32_t c = g < G ? (int32_t)cdiv((int64_t)(s_goff[g + 1] - s_goff[g]), (int64_t)(SW_THREADS * ITEMS)) : 0;
       int32_t incl = c;
       for (int d = 1; d < WAVE; d <<= 1) {
         const int32_t o = shfl_up(incl, d);
@@ -344,16 +347,16 @@ __device__ __forceinline__ void sweep_groups_body(const SweepArgs& a, SweepGroup
   }
   const int g = glo, pid = g / S, st = g - pid * S;
   const int32_t own_L = s_goff[g], own_R = s_goff[g + 1];
-  const int64_t base = own_L + (int64_t)(b - s_toff[g]) * SW_TILE;
-  const int64_t end = min<int64_t>(base + SW_TILE, own_R);
+  const int64_t base = own_L + (int64_t)(b - s_toff[g]) * (SW_THREADS * ITEMS);
+  const int64_t end = min<int64_t>(base + (SW_THREADS * ITEMS), own_R);
   const uint64_t tmask = (1ull << a.wb1) - 1;
   const uint64_t cm[3] = {s_cmask[0], s_cmask[1], s_cmask[2]};
 
-  uint64_t key[SW_ITEMS], tn[SW_ITEMS];
+  uint64_t key[ITEMS], tn[ITEMS];
   uint64_t m8 = 0;    // item j's active-stream mask in bits [8 j, 8 j + 8)
   uint32_t valid = 0;  // bit j: item j exists
 #pragma unroll
-  for (int j = 0; j < SW_ITEMS; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const int64_t i = base + (int64_t)j * SW_THREADS + tid;
     const bool ok = i < end;
     key[j] = ok ? a.ev[i] : ~0ull;
@@ -384,7 +387,7 @@ __device__ __forceinline__ void sweep_groups_body(const SweepArgs& a, SweepGroup
     if (cnt <= SB_CAP) {
       stage_keys(a.ev + c0, cnt, s_sib);
       __syncthreads();
-      sibling_search(a, s_sib, cnt, c0, L, s2, key, valid, m8, tn);
+      sibling_search<ITEMS>(a, s_sib, cnt, c0, L, s2, key, valid, m8, tn);
       __syncthreads();  // the next sibling's stretch overwrites this one
     } else {
       // every k-th key of the stretch in LDS: an item's lower bound lies
@@ -392,7 +395,7 @@ __device__ __forceinline__ void sweep_groups_body(const SweepArgs& a, SweepGroup
       const int32_t k = (int32_t)cdiv((int64_t)cnt, (int64_t)SB_CAP), ns = (int32_t)cdiv((int64_t)cnt, (int64_t)k);
       stage_keys(a.ev + c0, ns, s_sib, k);
       __syncthreads();
-      sibling_search_sampled(a, s_sib, ns, k, a.ev + c0, cnt, c0, L, s2, key, valid, m8, tn);
+      sibling_search_sampled<ITEMS>(a, s_sib, ns, k, a.ev + c0, cnt, c0, L, s2, key, valid, m8, tn);
       __syncthreads();
     }
   }
@@ -400,7 +403,7 @@ __device__ __forceinline__ void sweep_groups_body(const SweepArgs& a, SweepGroup
   uint32_t cur_m = 0;
   int64_t cur_len = 0;
 #pragma unroll
-  for (int j = 0; j < SW_ITEMS; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const uint32_t mj = (uint32_t)(m8 >> (8 * j)) & 255;
     if (!((valid >> j) & 1) || mj == 0 || tn[j] == ~0ull) continue;
     const int64_t len = (int64_t)tn[j] - (int64_t)((key[j] >> a.sb) & tmask);
@@ -647,7 +650,9 @@ static inline int64_t segoff_blocks(const Ctx& c) {
   return std::min<int64_t>(cdiv((int64_t)c.P * c.S + 1, 256 / WAVE), 1024);
 }
 // at most one partial tile per group beyond the full ones
-static inline int64_t sweep_groups_blocks(const Ctx& c) { return cdiv(c.ev_cap, SW_TILE) + (int64_t)c.P * c.S; }
+static inline int64_t sweep_groups_blocks(const Ctx& c, int items) {
+  return cdiv(c.ev_cap, SW_THREADS * items) + (int64_t)c.P * c.S;
+}
 static inline int64_t sweep_many_blocks(const Ctx& c) {
   return std::min<int64_t>(std::max<int64_t>(cdiv(c.ev_cap, SM_CHUNK), 1), SM_BLOCKS);
 }

@@ -4,7 +4,7 @@
 namespace hx {
 
 __global__ __launch_bounds__(PREP_THREADS) void k_prep(PrepArgs a) {
-  __shared__ PrepLds lds;
+  __shared__ PrepLds<PREP_ITEMS> lds;
   prep_body(a, lds, blockIdx.x);
 }
 
@@ -13,6 +13,6 @@ void launch_prep(Ctx& c) {
   hipLaunchKernelGGL(k_prep, dim3((unsigned)c.prep_tiles), dim3(PREP_THREADS), 0, c.st, prep_args(c));
 }
 
-int64_t prep_tile_rows() { return PREP_TILE; }
+int64_t prep_tile_rows(bool small) { return PREP_THREADS * (small ? PREP_ITEMS_SMALL : PREP_ITEMS); }
 
 }  // namespace hx

@@ -30,7 +30,8 @@ struct HistJob {
 };
 struct HistJobs {
   HistJob j[N_SORTS];
-  uint32_t* part;  // [N_SORTS][HIST_MAX_BLOCKS][8 * 256] per-workgroup counts
+  uint32_t* part;  // [N_SORTS][part_blocks][8 * 256] per-workgroup counts
+  int part_blocks;
   // the correlation table's plan and emptying, by the workgroups of slice
   // blockIdx.y == jt_slice
   int jt_slice;
@@ -187,12 +188,44 @@ __device__ __forceinline__ void hist_range(uint32_t* h, uint32_t* s_spare, uint6
   }
 }
 
+struct JtEmptyLds {
+  uint32_t s_direct;
+  int64_t s_slots;
+};
+
+// The correlation table's plan and its emptying, by gx workgroups of
+// HIST_THREADS.
+__device__ __forceinline__ void jt_empty_body(const HistJobs& jobs, DevState* ds, JtEmptyLds& lds, uint32_t bx,
+                                              uint32_t gx) {
+  auto& s_direct = lds.s_direct;
+  auto& s_slots = lds.s_slots;
+  // every workgroup takes the plan (the first stores it), then they empty
+  // the slots in use: launch and kernel words, and with hashed slots the
+  // claim words
+  if (threadIdx.x < WAVE) {
+    int64_t slots = 0;
+    const bool direct = jt_plan_wave(ds, jobs.jt_P, jobs.jt_cap, jobs.jt_hsize, bx == 0, &slots);
+    if (threadIdx.x == 0) {
+      s_direct = direct ? 1u : 0u;
+      s_slots = slots;
+    }
+  }
+  __syncthreads();
+  const int64_t q4 = cdiv(s_slots, 4);  // 16-byte words (the table is a multiple of 4 slots)
+  const bool claims = !s_direct;
+  const uint4 e4 = make_uint4(JT_EMPTY, JT_EMPTY, JT_EMPTY, JT_EMPTY);
+  for (int64_t w = (int64_t)bx * HIST_THREADS + threadIdx.x; w < q4; w += (int64_t)gx * HIST_THREADS) {
+    reinterpret_cast<uint4*>(jobs.jt_L)[w] = e4;
+    reinterpret_cast<uint4*>(jobs.jt_K)[w] = e4;
+    if (claims) reinterpret_cast<uint4*>(jobs.jt_C)[w] = e4;
+  }
+}
+
 struct DigitHistLds {
   uint32_t h[8 * 256];
   uint32_t s_spare[WAVE];  // adds that count nothing (never read)
   alignas(16) uint64_t s_row[HIST_THREADS * HIST_ROW];
-  uint32_t s_direct;
-  int64_t s_slots;
+  JtEmptyLds jt;
 };
 
 __device__ __forceinline__ void digit_hist_body(const HistJobs& jobs, DevState* ds, DigitHistLds& lds, uint32_t bx,
@@ -200,29 +233,8 @@ __device__ __forceinline__ void digit_hist_body(const HistJobs& jobs, DevState* 
   auto& h = lds.h;
   auto& s_spare = lds.s_spare;
   auto& s_row = lds.s_row;
-  auto& s_direct = lds.s_direct;
-  auto& s_slots = lds.s_slots;
   if ((int)by == jobs.jt_slice) {
-    // every workgroup takes the plan (the first stores it), then they empty
-    // the slots in use: launch and kernel words, and with hashed slots the
-    // claim words
-    if (threadIdx.x < WAVE) {
-      int64_t slots = 0;
-      const bool direct = jt_plan_wave(ds, jobs.jt_P, jobs.jt_cap, jobs.jt_hsize, bx == 0, &slots);
-      if (threadIdx.x == 0) {
-        s_direct = direct ? 1u : 0u;
-        s_slots = slots;
-      }
-    }
-    __syncthreads();
-    const int64_t q4 = cdiv(s_slots, 4);  // 16-byte words (the table is a multiple of 4 slots)
-    const bool claims = !s_direct;
-    const uint4 e4 = make_uint4(JT_EMPTY, JT_EMPTY, JT_EMPTY, JT_EMPTY);
-    for (int64_t w = (int64_t)bx * HIST_THREADS + threadIdx.x; w < q4; w += (int64_t)gx * HIST_THREADS) {
-      reinterpret_cast<uint4*>(jobs.jt_L)[w] = e4;
-      reinterpret_cast<uint4*>(jobs.jt_K)[w] = e4;
-      if (claims) reinterpret_cast<uint4*>(jobs.jt_C)[w] = e4;
-    }
+    jt_empty_body(jobs, ds, lds.jt, bx, gx);
     return;
   }
   const HistJob jb = jobs.j[by];
@@ -257,7 +269,7 @@ __device__ __forceinline__ void digit_hist_body(const HistJobs& jobs, DevState* 
     default: hist_range<8>(h, s_spare, s_row, jb.keys, lo, hi, jb.first, jb.sh1 - 8); break;
   }
   __syncthreads();
-  uint32_t* part = jobs.part + ((int64_t)jb.id * HIST_MAX_BLOCKS + blk) * 8 * 256;
+  uint32_t* part = jobs.part + ((int64_t)jb.id * jobs.part_blocks + blk) * 8 * 256;
   for (int j = threadIdx.x; j < jb.nd * 256; j += HIST_THREADS) part[j] = h[j];
   clear_status();
 }
@@ -286,7 +298,7 @@ __device__ __forceinline__ void hist_plan_body(const HistJobs& jobs, DevState* d
   const int64_t n = *jb.count;
   const int nblk = hist_blocks(n);
   const int lane = threadIdx.x & (WAVE - 1), grp = threadIdx.x / WAVE;
-  const uint4* src = reinterpret_cast<const uint4*>(jobs.part + (int64_t)jb.id * HIST_MAX_BLOCKS * 8 * 256 + d * 256) + lane;
+  const uint4* src = reinterpret_cast<const uint4*>(jobs.part + (int64_t)jb.id * jobs.part_blocks * 8 * 256 + d * 256) + lane;
   uint4 c4 = make_uint4(0u, 0u, 0u, 0u);
   for (int b0 = grp; b0 < nblk; b0 += PLAN_LOADS * PLAN_GROUPS) {
     uint4 v[PLAN_LOADS];
@@ -896,6 +908,7 @@ static inline HistJobs hist_jobs(const Ctx& c, SortBufs* const* s, const int32_t
                                  int* m_out, int* nd_out) {
   HistJobs jobs{};
   jobs.part = c.hist_part;
+  jobs.part_blocks = c.hist_blocks;
   int m = 0, nd = 0;
   int64_t n_max = 1;
   for (int i = 0; i < k; ++i) {

@@ -17,9 +17,10 @@
 
 namespace hx {
 
-constexpr int UN_THREADS = 1024;
+// Threads per tile: 1024 in general, 256 for small windows (more tiles than
+// the few of 4096 keys, and barriers over 4 waves instead of 16).
+constexpr int UN_THREADS = 1024, UN_THREADS_SMALL = 256;
 constexpr int UN_ITEMS = 4;
-constexpr int UN_TILE = UN_THREADS * UN_ITEMS;
 static_assert(UN_ITEMS % 4 == 0, "a thread's keys and rows are loaded 16 bytes at a time");
 
 struct UnionArgs {
@@ -75,6 +76,7 @@ __device__ __forceinline__ void put_gap(const UnionArgs& a, int64_t pos, int32_t
 
 // Events are staged in LDS at their position within the tile (the tile
 // then writes them out whole, coalesced).
+template <int UN_TILE>
 __device__ __forceinline__ void put_event(const UnionArgs& a, uint64_t* s_ev, int64_t pos, int32_t seg, int64_t t) {
   if (in_range(a.ds, pos, 2 * UN_TILE)) {
     const uint64_t pid = (uint64_t)(seg / a.S), stream = (uint64_t)(seg % a.S);
@@ -84,7 +86,7 @@ __device__ __forceinline__ void put_event(const UnionArgs& a, uint64_t* s_ev, in
 
 // Walks this thread's elements with the incoming carry.  MODE 0 counts gaps
 // and events and accumulates busy time; MODE 1 writes gaps and events.
-template <int MODE>
+template <int MODE, int UN_TILE>
 __device__ __forceinline__ void walk(const UnionArgs& a, const Elem* x, int nv, int32_t prev_seg, int32_t next_seg, uint64_t m_in,
                      int64_t i0, int64_t nK, uint32_t* ngap, uint32_t* nev, int64_t gbase, int64_t ebase,
                      int64_t* s_busy, int32_t seg0, uint64_t* s_ev) {
@@ -116,10 +118,10 @@ __device__ __forceinline__ void walk(const UnionArgs& a, const Elem* x, int nv, 
       }
       if (a.overlap && (m == 0 || q.s > C)) {
         if (m != 0) {
-          if (MODE == 1) put_event(a, s_ev, ebase + v, q.seg, C);
+          if (MODE == 1) put_event<UN_TILE>(a, s_ev, ebase + v, q.seg, C);
           ++v;
         }
-        if (MODE == 1) put_event(a, s_ev, ebase + v, q.seg, q.s);
+        if (MODE == 1) put_event<UN_TILE>(a, s_ev, ebase + v, q.seg, q.s);
         ++v;
       }
       if (MODE == 0) {
@@ -147,7 +149,7 @@ __device__ __forceinline__ void walk(const UnionArgs& a, const Elem* x, int nv, 
         ++g;
       }
       if (a.overlap && m != 0) {
-        if (MODE == 1) put_event(a, s_ev, ebase + v, q.seg, Cl);
+        if (MODE == 1) put_event<UN_TILE>(a, s_ev, ebase + v, q.seg, Cl);
         ++v;
       }
       if (full_gap && i0 + j == nK - 1) {
@@ -167,18 +169,20 @@ __device__ __forceinline__ void walk(const UnionArgs& a, const Elem* x, int nv, 
   *nev = v;
 }
 
+template <int NT>
 struct UnionLds {
   int s_tile;
-  uint64_t s_wv[UN_THREADS / WAVE];
+  uint64_t s_wv[NT / WAVE];
   uint64_t s_tile_excl;
   int64_t s_busy[64];
   int32_t s_seg0;
-  uint64_t s_scan[UN_THREADS / WAVE];
+  uint64_t s_scan[NT / WAVE];
   uint64_t s_base[2];
-  uint64_t s_ev[2 * UN_TILE];  // the tile's coverage-run endpoints, in order
+  uint64_t s_ev[2 * (NT * UN_ITEMS)];  // the tile's coverage-run endpoints, in order
 };
 
-__device__ __forceinline__ void union_body(const UnionArgs& a, UnionLds& lds, uint32_t bx) {
+template <int NT>
+__device__ __forceinline__ void union_body(const UnionArgs& a, UnionLds<NT>& lds, uint32_t bx) {
   auto& s_tile = lds.s_tile;
   auto& s_wv = lds.s_wv;
   auto& s_tile_excl = lds.s_tile_excl;
@@ -193,15 +197,15 @@ __device__ __forceinline__ void union_body(const UnionArgs& a, UnionLds& lds, ui
   const int par = (int)a.ds->sort_parity[a.sort_id];
   const uint64_t* keys = a.k[par];
   const uint32_t* vals = a.v[par];
-  const int64_t ntiles = nK > 0 ? cdiv(nK, UN_TILE) : 1;
+  const int64_t ntiles = nK > 0 ? cdiv(nK, (NT * UN_ITEMS)) : 1;
   if ((int64_t)bx >= ntiles) return;  // no tile: stay off the ticket counter
   const int tile = take_ticket(a.ds, a.ticket, &s_tile);
-  const int64_t base = (int64_t)tile * UN_TILE;
+  const int64_t base = (int64_t)tile * (NT * UN_ITEMS);
   const int nseg = a.P * a.S;
 
   if (nK == 0) {  // no kernels: one full-window gap per stream
     const bool full_gap = a.want_gaps && a.W > a.thr;
-    for (int s = tid; s < nseg; s += UN_THREADS)
+    for (int s = tid; s < nseg; s += NT)
       if (full_gap) put_gap(a, s, s, 0, a.W);
     if (tid == 0) {
       *a.gaps_out = full_gap ? nseg : 0;
@@ -306,7 +310,7 @@ __device__ __forceinline__ void union_body(const UnionArgs& a, UnionLds& lds, ui
   if (lane == WAVE - 1) s_wv[wv] = inc;
   __syncthreads();
   if (wv == 0) {
-    constexpr int NW = UN_THREADS / WAVE;
+    constexpr int NW = NT / WAVE;
     const uint64_t ws = wave_scan_u64(lane < NW ? s_wv[lane] : 0ull, 0ull, seg_max);
     const uint64_t we = wave_shift_up1_u64(ws, 0ull);
     if (lane < NW) s_wv[lane] = we;
@@ -319,11 +323,11 @@ __device__ __forceinline__ void union_body(const UnionArgs& a, UnionLds& lds, ui
   const uint64_t m_in = (has && (int32_t)OpSegMax::seg(pre) == x[0].seg) ? OpSegMax::m(pre) : 0;
 
   uint32_t ngap = 0, nev = 0;
-  if (has) walk<0>(a, x, nv, prev_seg, next_seg, m_in, i0, nK, &ngap, &nev, 0, 0, s_busy, s_seg0, s_ev);
+  if (has) walk<0, NT * UN_ITEMS>(a, x, nv, prev_seg, next_seg, m_in, i0, nK, &ngap, &nev, 0, 0, s_busy, s_seg0, s_ev);
   // gaps and endpoints before this thread's, in one scan (both counts of a
   // tile stay below 2^32)
   uint64_t tot;
-  const uint64_t before = block_excl_sum<UN_THREADS>(((uint64_t)ngap << 32) | nev, s_scan, &tot);
+  const uint64_t before = block_excl_sum<NT>(((uint64_t)ngap << 32) | nev, s_scan, &tot);
   const uint32_t gex = (uint32_t)(before >> 32), eex = (uint32_t)before;
   const uint32_t gtot = (uint32_t)(tot >> 32), etot = (uint32_t)tot;
   if (wv < 2) {
@@ -341,13 +345,13 @@ __device__ __forceinline__ void union_body(const UnionArgs& a, UnionLds& lds, ui
   }
   if (has && (ngap || nev)) {
     uint32_t g2, e2;
-    walk<1>(a, x, nv, prev_seg, next_seg, m_in, i0, nK, &g2, &e2, (int64_t)s_base[0] + gex, (int64_t)eex, s_busy, s_seg0,
+    walk<1, NT * UN_ITEMS>(a, x, nv, prev_seg, next_seg, m_in, i0, nK, &g2, &e2, (int64_t)s_base[0] + gex, (int64_t)eex, s_busy, s_seg0,
             s_ev);
   }
   __syncthreads();
   const uint32_t ne = etot;
   const int64_t eb = (int64_t)s_base[1];
-  for (uint32_t i = tid; i < ne; i += UN_THREADS)
+  for (uint32_t i = tid; i < ne; i += NT)
     if (in_range(a.ds, eb + i, a.ev_cap)) a.ev_keys[eb + i] = s_ev[i];
 }
 
