@@ -275,8 +275,9 @@ int herschel_workspace_size(int64_t n, const herschel_params *p, size_t *bytes);
 
 /* Reconstruct one window: n rows of ev under *p into *out.  Returns a
  * HERSCHEL_* code.  On EEVENT only counters->first_invalid is defined.
- * The work is ordered on p->hip_stream (it also runs on two library
- * streams that wait for, and are waited on by, that stream); the call
+ * The work is ordered on p->hip_stream (that of larger windows also runs on
+ * two library streams that wait for, and are waited on by, that stream; up
+ * to 450,000 rows it all runs on p->hip_stream); the call
  * returns once the device has finished all of it.  A call that launches
  * its kernels directly learns that from pinned host memory that its last
  * kernel writes (one small block per calling thread and device, allocated
@@ -355,7 +356,8 @@ int herschel_trace_analyze_chunked(const herschel_events *host, const int64_t *t
 
 const char *herschel_strerror(int code);
 
-/* Diagnostics for benchmarks.  Stages of one analysis call.  INIT, PREP,
+/* Diagnostics for benchmarks.  Stages of one analysis call (a call with a
+ * stage being timed is launched stage by stage whatever its size).  INIT, PREP,
  * HIST and SORT (with the refine pass after it) run in this order on
  * params->hip_stream; after SORT the JOIN, EDGES and NAMES stages run on a
  * library stream (JOIN beside the refine pass; with OUT_WAITS the op-name
@@ -399,7 +401,8 @@ int herschel_time_stage(int stage, void *start_event, void *stop_event);
  * 2 containment sort: out[3 * s + 0] = its keys, out[3 * s + 1] = bit mask
  * of the digits that no pass moved (bit d: every key agreed on digit d, or
  * digit d was left to the refine pass that orders keys equal above it; bit
- * 31 is set in the second case), out[3 * s + 2] = its digits.  Digits above
+ * 31 is set in the second case; all bits for a small window whose lists are
+ * sorted without digit passes), out[3 * s + 2] = its digits.  Digits above
  * digit 0 are 8 bits wide; digit 0 is 8 bits, or, when it is left to the
  * refine pass, the 8 to 14 bits below the passes' 8-bit digits.  out
  * must hold 9 entries (host memory).  Returns HERSCHEL_EINVAL for NULL

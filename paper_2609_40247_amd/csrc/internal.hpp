@@ -222,12 +222,12 @@ constexpr int AG_CHAIN = 64;
 // streams (us a call, level by level against three streams, traces of 4
 // streams: 150k rows 152 / 190, 300k 164 / 171, 450k 183 / 195, 600k 214 /
 // 200).  The smallest (up to TS_ROWS, TS_TILES tiles) also have their lists
-// sorted tile by tile (60k rows 120 against 140 us; with more tiles the
-// merge's search per key and tile costs more than it saves where the rows
-// come in no order: 120k shuffled rows 215 against 158).
+// sorted tile by tile (90k rows 129 against 154 us, 120k 144 against 154 in
+// delivery order and 152 against 156 in no order; with 64 tiles 240k rows
+// take 187 against 157).
 constexpr int64_t SMALL_ROWS = 450000;
 constexpr int TS_TILE = 4096;
-constexpr int TS_TILES = 16;
+constexpr int TS_TILES = 32;
 constexpr int64_t TS_ROWS = (int64_t)TS_TILE * TS_TILES;
 
 constexpr int RS_THREADS = 512;

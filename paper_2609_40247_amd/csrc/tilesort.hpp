@@ -4,18 +4,15 @@
 // 60k-row window).
 //
 //   tile sort: a workgroup sorts TS_TILE keys of a list in LDS (two passes of
-//              the radix passes' ranking over the top bits of the keys'
-//              range, then runs of equal bits by counting), and writes the
+//              the radix passes' ranking over the top bits that
+//              tell the keys apart, then runs of equal bits by counting), and writes the
 //              tile and every TS_STEP-th key of it;
-//   merge:     a workgroup takes TS_CHUNK consecutive keys of a sorted tile
-//              and finds, for every other tile, how many of its keys come
-//              before each of them: the sampled keys bound the stretch of
-//              the tile that can matter, which is staged in LDS and searched.
-//              The sum is the key's place.
+//   merge:     a thread per key counts, in every other tile, the keys that
+//              come before it; with its place in its own tile the sum is its
+//              place in the list.
 //
-// In a trace in delivery order a chunk's keys fall among those of a few tiles
-// only; in no order among all of them, and the merge costs a search per key
-// and tile, which is what bounds the number of tiles (TS_TILES).
+// The merge costs a search per key and tile, which bounds the number of tiles
+// (TS_TILES).
 #pragma once
 
 #include "internal.hpp"
@@ -28,15 +25,14 @@ constexpr int TS_WAVES = TS_THREADS / WAVE;
 constexpr int TS_STEP = TS_TILE / WAVE;  // keys between samples: a wave's lanes hold a tile's samples
 static_assert(TS_ITEMS * TS_THREADS == TS_TILE && TS_THREADS >= 256, "one thread per digit value");
 constexpr int TM_THREADS = 256;
-constexpr int TM_ITEMS = 2;
-constexpr int TS_CHUNK = TM_THREADS * TM_ITEMS;
-static_assert(TS_TILE % TS_CHUNK == 0, "chunks divide a tile");
+static_assert(TS_TILE % TM_THREADS == 0 && TS_STEP == 64, "a workgroup's keys lie in one tile; six search steps");
 
 struct TileSortJob {
   uint64_t* k[2];  // prep's list, and the result; the sorted tiles
   uint32_t* v[2];
   const int32_t* count;
   uint64_t* samples;  // [TS_TILES][WAVE]
+  int wb;             // bits of a key below its segment (pid and stream, thread or name)
   int contain;        // 1: ops of equal key by end time down, then row
   int id;
   uint32_t b0, m0;    // the list's first workgroup in the tile sort and in the merge
@@ -52,14 +48,25 @@ struct TileSortLds {
   uint32_t s_val[TS_TILE];
   uint32_t s_wh[TS_WAVES][256];  // per wave and digit value: counts, then places
   uint32_t s_scan[TS_WAVES];
-  uint64_t s_min[TS_WAVES], s_max[TS_WAVES];
+  uint64_t s_ext[4][TS_WAVES];
 };
 
-// One stable pass over the tile by 8 bits of (key - lo) >> sh.  Item j of
+// The bits of the tile's keys that tell them apart: segment and time, each
+// from the tile's smallest on, next to each other (a key's own layout has the
+// window's width between them, most of it unused by a tile).
+struct TileBits {
+  uint64_t seg0, t0, mask;
+  int wb, tb;  // bits below the segment in a key, and here
+  __device__ __forceinline__ uint64_t operator()(uint64_t k) const {
+    return (((k >> wb) - seg0) << tb) | ((k & mask) - t0);
+  }
+};
+
+// One stable pass over the tile by 8 bits of bits(key) >> sh.  Item j of
 // lane l is the tile's position (wave * TS_ITEMS + j) * 64 + l: items in
 // order, lanes in order is the tile's order.  Positions from tn on stay last.
 __device__ __forceinline__ void tile_pass(TileSortLds& lds, DevState* ds, uint64_t (&key)[TS_ITEMS],
-                                          uint32_t (&val)[TS_ITEMS], uint64_t lo, int sh, int tn) {
+                                          uint32_t (&val)[TS_ITEMS], const TileBits& bits, int sh, int tn) {
   const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
   const int p0 = wv * (TS_ITEMS * WAVE) + lane;
   auto& s_wh = lds.s_wh;
@@ -69,7 +76,7 @@ __device__ __forceinline__ void tile_pass(TileSortLds& lds, DevState* ds, uint64
   uint32_t rank[TS_ITEMS], dg[TS_ITEMS];
 #pragma unroll
   for (int j = 0; j < TS_ITEMS; ++j) {
-    dg[j] = p0 + j * WAVE < tn ? (uint32_t)((key[j] - lo) >> sh) & 255u : 255u;
+    dg[j] = p0 + j * WAVE < tn ? (uint32_t)(bits(key[j]) >> sh) & 255u : 255u;
     uint32_t mis_lo = 0, mis_hi = 0;  // lanes with another digit
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -143,29 +150,37 @@ __device__ __forceinline__ void tile_sort_body(const TileSortJobs& jobs, DevStat
     key[j] = jb.k[0][q];
     val[j] = jb.v[0][q];
   }
-  // the tile's smallest and largest key
-  uint64_t mn = key[0], mx = key[0];
+  // the tile's smallest and largest segment and time
+  TileBits bits;
+  bits.wb = jb.wb;
+  bits.mask = (1ull << jb.wb) - 1;
+  uint64_t ext[4] = {0, 0, 0, 0};  // largest ~segment, segment, ~time, time
 #pragma unroll
-  for (int j = 1; j < TS_ITEMS; ++j) {
-    mn = key[j] < mn ? key[j] : mn;
-    mx = key[j] > mx ? key[j] : mx;
+  for (int j = 0; j < TS_ITEMS; ++j) {
+    const uint64_t sg = key[j] >> jb.wb, tm = key[j] & bits.mask;
+    ext[0] = max(ext[0], ~sg);
+    ext[1] = max(ext[1], sg);
+    ext[2] = max(ext[2], ~tm);
+    ext[3] = max(ext[3], tm);
   }
-  mn = ~wave_allmax_u64(~mn);
-  mx = wave_allmax_u64(mx);
-  if (lane == 0) {
-    lds.s_min[wv] = mn;
-    lds.s_max[wv] = mx;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint64_t m = wave_allmax_u64(ext[i]);
+    if (lane == 0) lds.s_ext[i][wv] = m;
   }
   __syncthreads();
-  mn = ~wave_allmax_u64(~(lane < TS_WAVES ? lds.s_min[lane] : ~0ull));
-  mx = wave_allmax_u64(lane < TS_WAVES ? lds.s_max[lane] : 0ull);
-  // Two passes order the tile by the top 16 bits of the keys' range: with
-  // 4096 keys, few share them, and those that do count their way past one
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ext[i] = wave_allmax_u64(lane < TS_WAVES ? lds.s_ext[i][lane] : 0ull);
+  bits.seg0 = ~ext[0];
+  bits.t0 = ~ext[2];
+  bits.tb = bits_of(ext[3] - bits.t0);
+  const int rb = bits_of(ext[1] - bits.seg0) + bits.tb;
+  // Two passes order the tile by the top 16 of these bits: of 4096 keys few
+  // share them, and those that do count their way past one
   // another.  (Sorting every digit took five passes of about 3 us.)
-  const int rb = bits_of(mx - mn);
   int sh = rb > 16 ? rb - 16 : 0;
-  if (rb > 0) tile_pass(lds, ds, key, val, mn, sh, tn);
-  if (rb > 8) tile_pass(lds, ds, key, val, mn, sh + 8, tn);
+  if (rb > 0) tile_pass(lds, ds, key, val, bits, sh, tn);
+  if (rb > 8) tile_pass(lds, ds, key, val, bits, sh + 8, tn);
   __syncthreads();  // (the passes' reads of the tile)
 #pragma unroll
   for (int j = 0; j < TS_ITEMS; ++j) {
@@ -179,10 +194,10 @@ __device__ __forceinline__ void tile_sort_body(const TileSortJobs& jobs, DevStat
 #pragma unroll
     for (int j = 0; j < TS_ITEMS; ++j) {
       const int p = p0 + j * WAVE + TS_RUN;
-      if (p < tn) far |= ((s_key[p] - mn) >> sh) == ((key[j] - mn) >> sh);
+      if (p < tn) far |= (bits(s_key[p]) >> sh) == (bits(key[j]) >> sh);
     }
     if (__syncthreads_or(far)) {
-      for (int d = 0; d < rb; d += 8) tile_pass(lds, ds, key, val, mn, d, tn);
+      for (int d = 0; d < rb; d += 8) tile_pass(lds, ds, key, val, bits, d, tn);
       sh = 0;
       __syncthreads();
 #pragma unroll
@@ -197,17 +212,17 @@ __device__ __forceinline__ void tile_sort_body(const TileSortJobs& jobs, DevStat
   for (int j = 0; j < TS_ITEMS; ++j) {
     const int p = p0 + j * WAVE;
     if (p >= tn) continue;
-    const uint64_t k = key[j], h = (k - mn) >> sh;
+    const uint64_t k = key[j], h = bits(k) >> sh;
     const bool op = jb.contain && (k & 1) == 0;
     int to = p;
     for (int q = p - 1; q >= 0; --q) {  // those before that belong after
       const uint64_t o = s_key[q];
-      if (((o - mn) >> sh) != h) break;
+      if ((bits(o) >> sh) != h) break;
       to -= o > k || (op && o == k && jobs.te[s_val[q]] < jobs.te[val[j]]);
     }
     for (int q = p + 1; q < tn; ++q) {  // those after that belong before
       const uint64_t o = s_key[q];
-      if (((o - mn) >> sh) != h) break;
+      if ((bits(o) >> sh) != h) break;
       to += o < k || (op && o == k && jobs.te[s_val[q]] > jobs.te[val[j]]);
     }
     if (in_range(ds, to, tn)) {
@@ -218,157 +233,118 @@ __device__ __forceinline__ void tile_sort_body(const TileSortJobs& jobs, DevStat
   }
 }
 
-constexpr int TM_GRAN = 64;  // granules (TS_STEP keys) staged at a time
-
 struct TileMergeLds {
-  uint64_t s_key[TM_GRAN * TS_STEP];
-  uint32_t s_src[TM_GRAN];     // each staged granule's position in the list
-  uint32_t s_lo[TS_TILES];     // per tile: the first position that can matter,
-  uint32_t s_cnt[TS_TILES];    // keys from there on that can,
-  uint32_t s_off[TS_TILES];    // granules before them, over the tiles
-  uint64_t s_scan[TM_THREADS / WAVE];
+  uint64_t s_samp[TS_TILES][WAVE];
 };
+
+// One key per thread; TM_BATCH tiles are searched side by side, first their
+// samples in LDS, then the TS_STEP keys after the last sample that counts,
+// in memory (a wave's keys are neighbours, and so are the keys they read).
+// Staging the stretch of every other tile that a chunk of keys spans instead
+// took 20 us on a 60k-row window, but 60 where a long op, delivered at its
+// end, sorts in front of its tile and stretches the first chunk.
+constexpr int TM_BATCH = 8;
+static_assert(TS_TILES % TM_BATCH == 0, "whole batches of tiles");
 
 __device__ __forceinline__ void tile_merge_body(const TileSortJobs& jobs, DevState* ds, TileMergeLds& lds, uint32_t b) {
   int ji = 0;
   while (ji + 1 < jobs.m && b >= jobs.j[ji + 1].m0) ++ji;
   const TileSortJob& jb = jobs.j[ji];
   const int n = *jb.count;
-  const int first = (int)(b - jb.m0) * TS_CHUNK;  // the chunk's first position
+  const int first = (int)(b - jb.m0) * TM_THREADS;
   if (first >= n) return;
   const int tile = first / TS_TILE, tiles = (n + TS_TILE - 1) / TS_TILE;
-  const int cn = min(TS_CHUNK, min(n, (tile + 1) * TS_TILE) - first);
-  const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
-  constexpr int NW = TM_THREADS / WAVE;
-  auto& s_key = lds.s_key;
+  const int tid = threadIdx.x, i = min(first + tid, n - 1);
   const uint64_t* ks = jb.k[1];
   const uint32_t* vs = jb.v[1];
-  uint64_t key[TM_ITEMS];
-  uint32_t val[TM_ITEMS];
-  int pos[TM_ITEMS];
-#pragma unroll
-  for (int j = 0; j < TM_ITEMS; ++j) {
-    const int i = min(tid + j * TM_THREADS, cn - 1);
-    key[j] = ks[first + i];
-    val[j] = vs[first + i];
-    pos[j] = first - tile * TS_TILE + i;
-  }
-  const uint64_t kf = ks[first], kl = ks[first + cn - 1];
-  // Per other tile, from its samples (a lane each): the positions before lo
-  // hold keys below every key of the chunk, those from lo + cnt on above.
-  constexpr int TB = 8;  // tiles whose samples are in flight together
-  for (int t0 = wv; t0 < tiles; t0 += TB * NW) {
-    uint64_t s[TB];
-#pragma unroll
-    for (int u = 0; u < TB; ++u) {
-      const int t = min(t0 + u * NW, tiles - 1);
-      const int ns = (min(TS_TILE, n - t * TS_TILE) + TS_STEP - 1) / TS_STEP;
-      s[u] = jb.samples[t * WAVE + min(lane, ns - 1)];
-    }
-#pragma unroll
-    for (int u = 0; u < TB; ++u) {
-      const int t = t0 + u * NW;
-      if (t >= tiles) continue;  // uniform over the wave
-      const int len = min(TS_TILE, n - t * TS_TILE), ns = (len + TS_STEP - 1) / TS_STEP;
-      const int below = popc(ballot(lane < ns && s[u] < kf)), upto = popc(ballot(lane < ns && s[u] <= kl));
-      const int lo = max(below - 1, 0) * TS_STEP, hi = min(upto * TS_STEP, len);
-      if (lane == 0) {
-        lds.s_lo[t] = t == tile ? 0u : (uint32_t)lo;
-        lds.s_cnt[t] = t == tile ? 0u : (uint32_t)max(hi - lo, 0);
-      }
-    }
+  const uint64_t key = ks[i];
+  const uint32_t val = vs[i];
+  for (int x = tid; x < tiles * WAVE; x += TM_THREADS) {
+    const int t = x / WAVE, ns = (min(TS_TILE, n - t * TS_TILE) + TS_STEP - 1) / TS_STEP;
+    if (x % WAVE < ns) (&lds.s_samp[0][0])[x] = jb.samples[x];
   }
   __syncthreads();
-  static_assert(TS_TILES <= TM_THREADS, "one thread per tile");
-  const uint32_t ng_t = tid < tiles ? (lds.s_cnt[tid] + TS_STEP - 1) / TS_STEP : 0u;
-  const uint32_t lo_t = tid < tiles ? lds.s_lo[tid] : 0u;
-  // granules before each tile's, and the keys before all the stretches
-  uint64_t tot;
-  const uint64_t ex = block_excl_sum<TM_THREADS>(((uint64_t)lo_t << 32) | ng_t, lds.s_scan, &tot);
-  if (tid < tiles) lds.s_off[tid] = (uint32_t)ex;
-  const int ng = (int)(uint32_t)tot;
+  const bool op = jb.contain && (key & 1) == 0;
+  int pos = i - tile * TS_TILE;
+  // keys of equal value in an earlier tile come first (rows ascend from tile
+  // to tile)
+  for (int t0 = 0; t0 < tiles && tiles > 1; t0 += TM_BATCH) {  // uniform over the workgroup
+    int len[TM_BATCH], q[TM_BATCH], w[TM_BATCH];
+    auto counts = [&](int u, uint64_t x) { return t0 + u > tile ? x < key : x <= key; };
 #pragma unroll
-  for (int j = 0; j < TM_ITEMS; ++j) pos[j] += (int)(tot >> 32);
-  // The stretches' granules, TM_GRAN at a time, in LDS; a tile's part of
-  // them is one sorted segment.
-  for (int g0 = 0; g0 < ng; g0 += TM_GRAN) {  // uniform over the workgroup
-    const int g1 = min(ng, g0 + TM_GRAN);
-    __syncthreads();  // the offsets, and the last granules' reads
-    for (int q = (int)(uint32_t)ex; q < (int)((uint32_t)ex + ng_t); ++q)
-      if (q >= g0 && q < g1) lds.s_src[q - g0] = (uint32_t)(tid * TS_TILE) + lo_t + (uint32_t)(q - (int)(uint32_t)ex) * TS_STEP;
-    __syncthreads();
-    constexpr int GB = TM_GRAN / NW;  // granules per wave
-    uint64_t v[GB];
+    for (int u = 0; u < TM_BATCH; ++u) {
+      len[u] = t0 + u == tile ? 0 : max(0, min(TS_TILE, n - (t0 + u) * TS_TILE));
+      w[u] = (len[u] + TS_STEP - 1) / TS_STEP;
+      q[u] = 0;
+    }
+    for (int st = 0; st < 6; ++st) {  // the last sample that counts (or the first)
+      uint64_t x[TM_BATCH];
 #pragma unroll
-    for (int u = 0; u < GB; ++u) {
-      const int g = g0 + min(wv + u * NW, g1 - g0 - 1);
-      v[u] = ks[min((int)lds.s_src[g - g0] + lane, n - 1)];
+      for (int u = 0; u < TM_BATCH; ++u) x[u] = lds.s_samp[t0 + u][q[u] + (w[u] >> 1)];
+#pragma unroll
+      for (int u = 0; u < TM_BATCH; ++u) {
+        const int half = w[u] >> 1;
+        q[u] = counts(u, x[u]) ? q[u] + half : q[u];
+        w[u] -= half;
+      }
+    }
+    bool some[TM_BATCH];
+#pragma unroll
+    for (int u = 0; u < TM_BATCH; ++u) {
+      some[u] = len[u] > 0 && counts(u, lds.s_samp[t0 + u][q[u]]);
+      q[u] = some[u] ? q[u] * TS_STEP : 0;
+      w[u] = some[u] ? min(TS_STEP, len[u] - q[u]) : 0;  // the key at q counts
+    }
+    for (int st = 0; st < 6; ++st) {  // the last key that counts
+      uint64_t x[TM_BATCH];
+#pragma unroll
+      for (int u = 0; u < TM_BATCH; ++u) x[u] = ks[min((t0 + u) * TS_TILE + q[u] + (w[u] >> 1), n - 1)];
+#pragma unroll
+      for (int u = 0; u < TM_BATCH; ++u) {
+        const int half = w[u] >> 1;
+        q[u] = half > 0 && counts(u, x[u]) ? q[u] + half : q[u];
+        w[u] -= half;
+      }
     }
 #pragma unroll
-    for (int u = 0; u < GB; ++u) s_key[(wv + u * NW) * TS_STEP + lane] = v[u];
-    __syncthreads();
-    for (int t = 0; t < tiles; ++t) {  // uniform over the workgroup
-      const int off = (int)lds.s_off[t], cnt_t = (int)lds.s_cnt[t];
-      const int ga = max(off, g0), gb = min(off + (cnt_t + TS_STEP - 1) / TS_STEP, g1);
-      if (ga >= gb) continue;
-      const uint64_t* seg = s_key + (ga - g0) * TS_STEP;
-      const int seg0 = (ga - off) * TS_STEP;                 // the segment's first key in the stretch
-      const int cnt = min((gb - off) * TS_STEP, cnt_t) - seg0;
-      // keys of equal value in an earlier tile come first (rows ascend from
-      // tile to tile)
-      const bool later = t > tile;
-      auto counts = [&](uint64_t x, uint64_t k) { return later ? x < k : x <= k; };
-      int q[TM_ITEMS];
+    for (int u = 0; u < TM_BATCH; ++u) q[u] += some[u] ? 1 : 0;  // keys that count
+    if (op) {
+      // ops that start together: the run of equal keys (before q in an
+      // earlier tile, from q on in a later one) is in end time order; those
+      // that end later come first, in an earlier tile also those that end
+      // as late
+      uint64_t x[TM_BATCH];
 #pragma unroll
-      for (int j = 0; j < TM_ITEMS; ++j) q[j] = 0;
-      for (int w = cnt; w > 1;) {
-        const int half = w >> 1;
-        uint64_t x[TM_ITEMS];
+      for (int u = 0; u < TM_BATCH; ++u)
+        x[u] = ks[min((t0 + u) * TS_TILE + max(q[u] - (t0 + u > tile ? 0 : 1), 0), n - 1)];
 #pragma unroll
-        for (int j = 0; j < TM_ITEMS; ++j) x[j] = seg[q[j] + half];
-#pragma unroll
-        for (int j = 0; j < TM_ITEMS; ++j) q[j] = counts(x[j], key[j]) ? q[j] + half : q[j];
-        w -= half;
-      }
-#pragma unroll
-      for (int j = 0; j < TM_ITEMS; ++j) {
-        int r = q[j] + (counts(seg[q[j]], key[j]) ? 1 : 0);  // keys that count
-        if (jb.contain && (key[j] & 1) == 0) {
-          // ops that start together: the segment's run of equal keys (before
-          // r in an earlier tile, from r on in a later one) is in end time
-          // order; those that end later come first, in an earlier tile also
-          // those that end as late
-          int a = r, e = r;
-          if (later)
-            while (e < cnt && seg[e] == key[j]) ++e;
+      for (int u = 0; u < TM_BATCH; ++u) {
+        const bool later = t0 + u > tile;
+        if (len[u] == 0 || x[u] != key || (later ? q[u] >= len[u] : q[u] == 0)) continue;
+        const int tb = (t0 + u) * TS_TILE;
+        int a = q[u], e = q[u];
+        if (later)
+          while (e < len[u] && ks[tb + e] == key) ++e;
+        else
+          while (a > 0 && ks[tb + a - 1] == key) --a;
+        const int64_t own = jobs.te[val];
+        while (a < e) {
+          const int mid = (a + e) >> 1;
+          const int64_t o = jobs.te[vs[tb + mid]];
+          if (later ? o > own : o >= own)
+            a = mid + 1;
           else
-            while (a > 0 && seg[a - 1] == key[j]) --a;
-          if (a < e) {
-            const int64_t own = jobs.te[val[j]];
-            const uint32_t* sv = vs + t * TS_TILE + (int)lds.s_lo[t] + seg0;
-            int y = e;
-            while (a < y) {
-              const int mid = (a + y) >> 1;
-              const int64_t o = jobs.te[sv[mid]];
-              if (later ? o > own : o >= own)
-                a = mid + 1;
-              else
-                y = mid;
-            }
-            r = a;
-          }
+            e = mid;
         }
-        pos[j] += r;
+        q[u] = a;
       }
     }
-  }
 #pragma unroll
-  for (int j = 0; j < TM_ITEMS; ++j) {
-    if (tid + j * TM_THREADS >= cn) continue;
-    if (in_bounds(ds, pos[j], n)) {
-      jb.k[0][pos[j]] = key[j];
-      jb.v[0][pos[j]] = val[j];
-    }
+    for (int u = 0; u < TM_BATCH; ++u) pos += q[u];
+  }
+  if (first + tid < n && in_bounds(ds, pos, n)) {
+    jb.k[0][pos] = key;
+    jb.v[0][pos] = val;
   }
 }
 
@@ -382,10 +358,12 @@ static inline TileSortJobs tile_sort_jobs(const Ctx& c, SortBufs* const* s, cons
   uint64_t* samples = reinterpret_cast<uint64_t*>(c.hist_part);
   for (int i = 0; i < k; ++i) {
     jobs.j[jobs.m++] = TileSortJob{{s[i]->k[0], s[i]->k[1]}, {s[i]->v[0], s[i]->v[1]}, count[i],
-                                   samples + (int64_t)s[i]->id * tiles * WAVE, s[i]->id == SORT_C ? 1 : 0,
+                                   samples + (int64_t)s[i]->id * tiles * WAVE,
+                                   s[i]->id == SORT_E ? c.wb1 : c.wb + (s[i]->id == SORT_C ? 1 : 0),
+                                   s[i]->id == SORT_C ? 1 : 0,
                                    s[i]->id, (uint32_t)b, (uint32_t)m};
     b += tiles;
-    m += tiles * (TS_TILE / TS_CHUNK);
+    m += tiles * (TS_TILE / TM_THREADS);
   }
   *sort_grid = b;
   *merge_grid = m;

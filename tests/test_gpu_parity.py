@@ -365,6 +365,66 @@ def test_overlap_beyond_8_streams(H, S, P, rows, window):
     check(H, cols, tr.params, f"{S} streams, {P} processes")
 
 
+@pytest.mark.parametrize("rows,times", [(r, "spread") for r in (1, 63, 4096, 4097, 8193, 32_767, 40_000, 131_071,
+                                                               131_072, 131_073, 449_999, 450_000, 450_001)] +
+                         [(r, t) for r in (4097, 40_000, 131_072) for t in ("grid", "cluster")])
+def test_small_window_sorts(H, rows, times):
+    """Sizes around the tiles of the tile sort (4096 keys a tile, eight tiles
+    searched together, 32 tiles at most) and around the largest window that is
+    launched level by level; start times spread, on a coarse grid (long runs of
+    equal keys across tiles, ops among them ordered by end time) and mostly in
+    a cluster with outliers (runs that the tile sort's counting hands to its
+    full sort)."""
+    tr = synth.random_small(9800 + rows, n_rows=rows, window=1 << 31, n_procs=2, n_streams=5, n_threads=3,
+                            corr_range=max(rows // 2, 1), flags=7)
+    cols = tr.columns()
+    dur = cols["te"] - cols["ts"]
+    w0 = tr.params["window_begin"]
+    if times == "grid":
+        step = (1 << 31) // 37
+        cols["ts"] = w0 + (cols["ts"] - w0) // step * step
+    elif times == "cluster":
+        near = np.random.default_rng(rows).random(rows) < 0.995
+        cols["ts"] = np.where(near, w0 + 1000 + (cols["ts"] - w0) % 3000, cols["ts"])
+    cols["te"] = cols["ts"] + dur % 5_000_000
+    check(H, cols, tr.params, f"{rows} rows, {times}")
+
+
+THREE_STREAMS = {
+    "long runs": lambda H: test_long_runs_of_equal_op_starts(H),
+    "short runs across tiles": lambda H: test_wide_keys_short_runs_across_tiles(H),
+    "deep nesting": lambda H: test_deep_nesting(H),
+    "medium": lambda H: test_random_medium_spans_tiles(H, 1),
+    "config0": lambda H: test_config0(H),
+    "bursty streams": lambda H: test_bursty_streams_overlap(H, 0),
+    "sparse beside dense": lambda H: test_sparse_stream_beside_dense_streams(H, 0),
+    "stretch at capacity": lambda H: test_overlap_stretch_at_lds_capacity(H, 4097),
+    "33 processes": lambda H: test_overlap_group_count_limit(H, 33),
+    "64 streams": lambda H: test_64_streams_overlap(H),
+    "sparse ids": lambda H: test_sparse_correlation_ids(H, 0),
+    "empty": lambda H: test_empty_and_all_outside(H),
+    "idle coincidence": lambda H: test_idle_coincidence_workloads(H, "medium"),
+    "critical path": lambda H: test_crit_workloads(H, "all outputs"),
+    "graph replays": lambda H: test_graph_replay_workloads(H, "all outputs"),
+}
+
+
+@pytest.mark.parametrize("which", sorted(THREE_STREAMS))
+def test_small_windows_on_three_streams(H, which):
+    """The kernels of the larger windows on small ones: a call with a stage
+    being timed is not launched level by level."""
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in ev:
+        e.record()
+    torch.cuda.synchronize()
+    assert H.herschel_time_stage(H.STAGES.index("final"), *ev) == 0
+    try:
+        THREE_STREAMS[which](H)
+    finally:
+        torch.cuda.synchronize()
+        H.herschel_time_stage(H.STAGES.index("final"), None, None)
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_sparse_correlation_ids(H, seed):
     """The same traces with every correlation id spread by 2^30: no id table
