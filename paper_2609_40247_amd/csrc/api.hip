@@ -213,11 +213,11 @@ size_t layout_workspace(Ctx& c, char* base) {
   return b.off;
 }
 
-// Exits the critical path's walk follows per process before the doubling
-// pass takes over ($HERSCHEL_CRIT_WALK, for tests of that pass; 64 by default).
+// Exits the critical path's walk follows per process before the strides
+// take over ($HERSCHEL_CRIT_WALK, for tests of what follows; 64 by default).
 static int crit_walk_max() {
   const char* e = getenv("HERSCHEL_CRIT_WALK");
-  if (!e || !*e) return 64;
+  if (!e || !*e) return CP_WALK;
   const long v = strtol(e, nullptr, 10);
   return v < 0 ? 0 : v > (1L << 20) ? (1 << 20) : (int)v;
 }
@@ -740,11 +740,19 @@ static int wait_mailbox(hipStream_t st, Mailbox* mb, int64_t seq, herschel_count
   return HERSCHEL_OK;
 }
 
-// The critical path's doubling pass when the call left it out and a walk
-// stopped short (DevState::crit_more), on the caller's stream, waited for.
+// The rest of the critical path's marking when the call left it out and a
+// walk stopped short (DevState::crit_more), on the caller's stream, waited
+// for: the strides, and the doubling if those stop short as well.
 static int finish_crit(Ctx& c, uint32_t more) {
   if (!c.crit_deferred || !more) return HERSCHEL_OK;
-  launch_crit_deferred(c);
+  if (!c.small) {
+    launch_crit_deferred(c, false);
+    if (hipMemcpyAsync(&more, &c.ds->crit_more, sizeof(more), hipMemcpyDeviceToHost, c.st) != hipSuccess ||
+        hipGetLastError() != hipSuccess || hipStreamSynchronize(c.st) != hipSuccess)
+      return HERSCHEL_EDEVICE;
+  }
+  if (!(more & 2u)) return HERSCHEL_OK;
+  launch_crit_deferred(c, true);
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(c.st) != hipSuccess) return HERSCHEL_EDEVICE;
   return HERSCHEL_OK;
 }
@@ -902,7 +910,7 @@ int herschel_trace_analyze(const herschel_events* ev, int64_t n, const herschel_
     code = wait_mailbox(c.st, c.mailbox, c.mailbox_seq, &h);
     if (code == HERSCHEL_OK) {
       have = true;
-      more = __atomic_load_n(&c.mailbox->crit_more, __ATOMIC_RELAXED) != 0;
+      more = (uint32_t)__atomic_load_n(&c.mailbox->crit_more, __ATOMIC_RELAXED);
     } else if (code != MAILBOX_MISSED) {
       return code;
     }

@@ -32,10 +32,13 @@
 // the tile; one thread per process walks the exits from its last event and
 // marks each one (the entries of the path into tiles); a workgroup per tile
 // that holds a marked entry marks its chain inside the tile.  A path with
-// more than walk_max exits left after the walk is marked by pointer
-// doubling over the exits from the marked ones (round r marks the exits
-// 2^r steps behind while the pointers double, until a round adds nothing),
-// and the tiles are marked again.  A last pass charges the marked steps.
+// more than walk_max exits (rows in no order put an exit at nearly every
+// step) is walked again in strides of CP_STRIDE exits, over pointers squared
+// CP_SQUARES times, and a thread per stride marks the exits inside it; one
+// with more than hop_max strides is marked by pointer doubling over the exits
+// from the marked ones (round r marks the exits 2^r steps behind while the
+// pointers double, until a round adds nothing).  Then the tiles are marked
+// again.  A last pass charges the marked steps.
 #include "internal.hpp"
 
 namespace hx {
@@ -90,9 +93,17 @@ struct CritArgs {
   uint8_t* crit_flags;
   int64_t* crit_proc;
   int round;
-  int walk_max;  // exits a process's walk marks before the doubling takes over
-  bool final;    // the path is completely marked when the charging pass runs
+  int walk_max;  // exits a process's walk marks before the strides take over
+  int hop_max;   // strides of a process's path before the doubling takes over
+  int32_t* sq;   // [2n] squared pointers, with ptr0 in turn (the kernel ends' buffer)
+  uint32_t left; // the charging pass waits while one of these bits of crit_more is set
 };
+
+// DevState::crit_more: a walk stopped short, and so did the strides.
+enum : uint32_t { CP_MORE_STRIDES = 1, CP_MORE_DOUBLING = 2 };
+constexpr int CP_SQUARES = 5;
+constexpr int CP_STRIDE = 1 << CP_SQUARES;
+constexpr int CP_HOPS = 512;
 
 // Tiles of event ids for the two-level marking: CP_TE ids per workgroup of
 // CP_LT threads, in LDS.
@@ -431,7 +442,7 @@ __global__ __launch_bounds__(CP_LT) void k_crit_local(CritArgs a) {
 // Each process's path from E of its last-ending record: the exits, walked
 // one after another and marked (they are the path's entries into tiles).
 // After walk_max exits the walk marks where it stands and leaves the rest to
-// the doubling.
+// the strides.
 __global__ __launch_bounds__(256) void k_crit_walk(CritArgs a) {
   const int p = blockIdx.x * 256 + threadIdx.x;
   if (p >= a.P) return;
@@ -442,10 +453,64 @@ __global__ __launch_bounds__(256) void k_crit_walk(CritArgs a) {
   for (int s = 0; e >= 0 && in_range(a.ds, e, ne); ++s) {
     a.mark[e] = 1;
     if (s >= a.walk_max) {
-      atomicOr(&a.ds->crit_more, 1u);
+      atomicOr(&a.ds->crit_more, (uint32_t)CP_MORE_STRIDES);
       break;
     }
     e = a.ptr1[e];
+  }
+}
+
+// One squaring of the exit pointers: out[e] = in[in[e]].
+__global__ __launch_bounds__(256) void k_crit_square(CritArgs a) {
+  if (!a.ds->crit_more) return;
+  const int32_t* in = a.round == 0 ? a.ptr1 : (a.round & 1) ? a.ptr0 : a.sq;
+  int32_t* out = (a.round & 1) ? a.sq : a.ptr0;
+  const int64_t ne = 2 * a.n;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ne; i += (int64_t)gridDim.x * 256) {
+    const int32_t t = in[i];
+    out[i] = t >= 0 && in_range(a.ds, t, ne) ? in[t] : -1;
+  }
+}
+static_assert(CP_SQUARES % 2 == 1, "the last squaring writes ptr0");
+
+// The same pointers by following the exits CP_STRIDE times.
+__global__ __launch_bounds__(256) void k_crit_jump(CritArgs a) {
+  if (!a.ds->crit_more) return;
+  const int64_t ne = 2 * a.n;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ne; i += (int64_t)gridDim.x * 256) {
+    int64_t e = i;
+    for (int k = 0; k < CP_STRIDE && e >= 0 && in_range(a.ds, e, ne); ++k) e = a.ptr1[e];
+    a.ptr0[i] = (int32_t)e;
+  }
+}
+
+// Each process's path again, CP_STRIDE exits at a time, by one thread of a
+// workgroup; then a thread per stride marks the exits inside it.
+__global__ __launch_bounds__(CP_HOPS) void k_crit_strides(CritArgs a) {
+  __shared__ int32_t s_hop[CP_HOPS];
+  __shared__ int s_n;
+  if (!a.ds->crit_more) return;
+  const int64_t ne = 2 * a.n;
+  for (int p = blockIdx.x; p < a.P; p += gridDim.x) {
+    __syncthreads();  // the last process's reads
+    if (threadIdx.x == 0) {
+      const uint32_t z = a.zrow1[p];
+      int64_t e = z ? 2 * (int64_t)(z - 1) + 1 : -1;
+      int s = 0;
+      for (; s < a.hop_max && e >= 0 && in_range(a.ds, e, ne); ++s) {
+        s_hop[s] = (int32_t)e;
+        e = a.ptr0[e];
+      }
+      s_n = s;
+      if (e >= 0) atomicOr(&a.ds->crit_more, (uint32_t)CP_MORE_DOUBLING);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x >= s_n) continue;
+    int64_t e = s_hop[threadIdx.x];
+    for (int k = 0; k < CP_STRIDE && e >= 0 && in_range(a.ds, e, ne); ++k) {
+      a.mark[e] = 1;
+      e = a.ptr1[e];
+    }
   }
 }
 
@@ -503,13 +568,13 @@ __global__ __launch_bounds__(CP_MLT) void k_crit_mark_local(CritArgs a) {
   }
 }
 
-// One doubling round over the exits (only when a walk stopped short): every
+// One doubling round over the exits (only when the strides stopped short): every
 // marked event marks the event its pointer names (2^round exits back), and
 // every pointer is replaced by its target's.  A round after one that marked
 // nothing does nothing: the path's entries are marked.
 __global__ __launch_bounds__(256) void k_crit_round(CritArgs a) {
   const int rd = a.round;
-  if (!a.ds->crit_more) return;
+  if (!(a.ds->crit_more & CP_MORE_DOUBLING)) return;
   if (rd > 0 && a.ds->crit_new[rd - 1] == 0) return;
   const int32_t* in = rd == 0 ? a.ptr1 : (rd & 1) ? a.ptr0 : a.ptr1;
   int32_t* out = (rd & 1) ? a.ptr1 : a.ptr0;
@@ -539,7 +604,7 @@ __global__ __launch_bounds__(256) void k_crit_round(CritArgs a) {
 // Each of the three outputs may be NULL.
 __global__ __launch_bounds__(256) void k_crit_attr(CritArgs a) {
   __shared__ unsigned long long s_part[CP_LDS_PROCS * CP_PARTS];
-  if (!a.final && a.ds->crit_more) return;  // the doubling comes first
+  if (a.ds->crit_more & a.left) return;  // the path is not completely marked yet
   int64_t* const proc = a.crit_proc;
   const bool lds = proc && a.P <= CP_LDS_PROCS;
   if (lds)
@@ -622,7 +687,11 @@ static CritArgs crit_args(Ctx& c) {
   a.crit_proc = c.o.crit_proc;
   a.round = 0;
   a.walk_max = c.crit_walk_max;
-  a.final = !c.crit_deferred;
+  a.left = CP_MORE_STRIDES | CP_MORE_DOUBLING;
+  // the kernel ends' buffer is free once the host records' pass is done
+  a.sq = reinterpret_cast<int32_t*>(c.sE.k[0]);
+  // (a lower walk limit, for tests, limits the strides as well)
+  a.hop_max = c.crit_walk_max < CP_WALK ? c.crit_walk_max : CP_HOPS;
   return a;
 }
 
@@ -642,22 +711,36 @@ int crit_rounds(int64_t n) {
   return r;
 }
 
-// The doubling over the exits, the tiles marked again, the charges.
-static void launch_crit_rest(Ctx& c, CritArgs a) {
-  const int rounds = crit_rounds(c.n);
-  for (int rd = 0; rd < rounds; ++rd) {
-    a.round = rd;
-    hipLaunchKernelGGL(k_crit_round, dim3(crit_grid(2 * c.n)), dim3(256), 0, c.st, a);
-  }
-  const unsigned tiles = (unsigned)cdiv(2 * c.n, CP_TE);
-  hipLaunchKernelGGL(k_crit_mark_local, dim3(tiles), dim3(CP_MLT), 0, c.st, a);
-  a.final = true;
+static void launch_crit_marks(Ctx& c, CritArgs a, uint32_t left) {
+  a.left = left;
+  hipLaunchKernelGGL(k_crit_mark_local, dim3((unsigned)cdiv(2 * c.n, CP_TE)), dim3(CP_MLT), 0, c.st, a);
   hipLaunchKernelGGL(k_crit_attr, dim3(crit_grid(c.n)), dim3(256), 0, c.st, a);
 }
 
-// With c.crit_deferred the doubling is left out: the charging pass then
-// does nothing if a walk stopped short (DevState::crit_more), and the caller
-// runs launch_crit_deferred once the call has ended.
+// The strides.  The pointers of a small window stay in the caches, and one
+// launch that follows 32 exits per event takes half of five squarings.
+static void launch_crit_strides(Ctx& c, CritArgs a) {
+  if (c.small) {
+    hipLaunchKernelGGL(k_crit_jump, dim3((unsigned)cdiv(2 * c.n, 256)), dim3(256), 0, c.st, a);
+  } else {
+    for (a.round = 0; a.round < CP_SQUARES; ++a.round)
+      hipLaunchKernelGGL(k_crit_square, dim3(crit_grid(2 * c.n)), dim3(256), 0, c.st, a);
+  }
+  hipLaunchKernelGGL(k_crit_strides, dim3((unsigned)std::min(c.P, 2048)), dim3(CP_HOPS), 0, c.st, a);
+}
+
+// The doubling over the exits.
+static void launch_crit_rounds(Ctx& c, CritArgs a) {
+  const int rounds = crit_rounds(c.n);
+  for (a.round = 0; a.round < rounds; ++a.round)
+    hipLaunchKernelGGL(k_crit_round, dim3(crit_grid(2 * c.n)), dim3(256), 0, c.st, a);
+}
+
+// With c.crit_deferred the doubling, and but for small windows the strides,
+// are left out: the charging pass then does nothing if a walk stopped short
+// (DevState::crit_more), and the caller runs launch_crit_deferred once the
+// call has ended.  (A small window's strides are two launches, 5 us when they
+// have nothing to do and a round trip to the host less when they have.)
 void launch_crit_kernels(Ctx& c) {
   if (c.n == 0) return;
   hipLaunchKernelGGL(k_crit_kernels, dim3(crit_grid(c.n)), dim3(256), 0, c.st, crit_args(c));
@@ -675,21 +758,32 @@ void launch_crit(Ctx& c) {
   if (c.n == 0) return;
   CritArgs a = crit_args(c);
   hipLaunchKernelGGL(k_crit_rows, dim3(crit_grid(c.n)), dim3(256), 0, c.st, a);
-  const unsigned tiles = (unsigned)cdiv(2 * c.n, CP_TE);
-  hipLaunchKernelGGL(k_crit_local, dim3(tiles), dim3(CP_LT), 0, c.st, a);
+  hipLaunchKernelGGL(k_crit_local, dim3((unsigned)cdiv(2 * c.n, CP_TE)), dim3(CP_LT), 0, c.st, a);
   hipLaunchKernelGGL(k_crit_walk, dim3((unsigned)cdiv(c.P, 256)), dim3(256), 0, c.st, a);
   if (!c.crit_deferred) {
-    launch_crit_rest(c, a);
+    launch_crit_strides(c, a);
+    launch_crit_rounds(c, a);
+    launch_crit_marks(c, a, 0);
     return;
   }
-  hipLaunchKernelGGL(k_crit_mark_local, dim3(tiles), dim3(CP_MLT), 0, c.st, a);
-  hipLaunchKernelGGL(k_crit_attr, dim3(crit_grid(c.n)), dim3(256), 0, c.st, a);
+  if (c.small) {
+    launch_crit_strides(c, a);
+    launch_crit_marks(c, a, CP_MORE_DOUBLING);
+  } else {
+    launch_crit_marks(c, a, CP_MORE_STRIDES | CP_MORE_DOUBLING);
+  }
 }
 
-void launch_crit_deferred(Ctx& c) {
+void launch_crit_deferred(Ctx& c, bool doubling) {
   if (c.n == 0) return;
   CritArgs a = crit_args(c);
-  launch_crit_rest(c, a);
+  if (doubling) {
+    launch_crit_rounds(c, a);
+    launch_crit_marks(c, a, 0);
+  } else {
+    launch_crit_strides(c, a);
+    launch_crit_marks(c, a, CP_MORE_DOUBLING);
+  }
 }
 
 }  // namespace hx

@@ -52,6 +52,9 @@ struct Mailbox {
   int64_t seq;
 };
 
+// Exits that a process's critical-path walk follows one by one.
+constexpr int CP_WALK = 64;
+
 struct Ctx {
   hipStream_t st = nullptr;
   Mailbox* mailbox = nullptr;  // NULL: the caller copies the counters back itself
@@ -141,8 +144,8 @@ struct Ctx {
   uint8_t* crit_code = nullptr;      // [2n] its part and charged record
   uint8_t* crit_mark = nullptr;      // [2n] on the path (zeroed)
   int32_t* crit_ptr[2] = {nullptr, nullptr};  // [2n] exits, then doubling pointers
-  int crit_walk_max = 64;            // exits a process's walk follows before the doubling takes over
-  bool crit_deferred = false;        // the doubling pass, if needed, is enqueued after the call
+  int crit_walk_max = CP_WALK;       // exits a process's walk follows before the strides take over
+  bool crit_deferred = false;        // the strides and the doubling, if needed, are enqueued after the call
   uint32_t* crit_lastc1 = nullptr;   // [n] by containment position (zeroed)
   uint8_t* crit_hasnext = nullptr;   // [n] by containment position (zeroed)
   uint64_t* crit_zmax = nullptr;     // [P] (zeroed)
@@ -180,7 +183,7 @@ void launch_depth(Ctx& c);
 void launch_opagg(Ctx& c);
 void launch_names_reduce(Ctx& c);
 void launch_kernel_ops(Ctx& c);
-void launch_crit_deferred(Ctx& c);
+void launch_crit_deferred(Ctx& c, bool doubling);
 void launch_opnames(Ctx& c);
 bool opnames_use_tables(int NOP);
 int opnames_block_count(int64_t n_max, int NOP);
