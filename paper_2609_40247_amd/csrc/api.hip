@@ -402,17 +402,7 @@ static int enqueue_locked(Ctx& c, DeviceStreams* dsx) {
 
   if (c.small) {
     launch_levels(c, ss, cc, ks, p_shared);
-    if (c.waits) {
-      launch_dg_scan(c);
-      launch_waits(c);
-    }
-    if (c.sol) launch_sol(c);
-    if (c.crit) {
-      launch_crit_kernels(c);
-      launch_crit_front(c);
-      launch_crit(c);
-    }
-    if (c.graph) launch_graph(c);
+    if (c.crit) launch_crit_walk(c);
     launch_finalize(c);
     return hipGetLastError() == hipSuccess ? HERSCHEL_OK : HERSCHEL_EDEVICE;
   }

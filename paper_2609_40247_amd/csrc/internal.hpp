@@ -199,6 +199,7 @@ void launch_crit_elist(Ctx& c);
 void launch_crit_kernels(Ctx& c);
 void launch_crit_front(Ctx& c);
 void launch_crit(Ctx& c);
+void launch_crit_walk(Ctx& c);
 void launch_graph(Ctx& c);
 bool graph_uses_tables(int NG);
 int graph_block_count(int64_t n_max, int NG);
@@ -208,7 +209,7 @@ bool sol_uses_tables(int NOP);
 int64_t prep_tile_rows(bool small);
 int64_t union_tile_elems(bool small);
 void names_set_lds_attr();
-// small windows: everything up to the per-op aggregates, fused level by level
+// small windows: the call up to the critical path's walk, fused level by level
 void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks, int passes);
 void level_set_lds_attr();
 

@@ -16,21 +16,27 @@
 // A body's tiles wait only for tiles of lower index (look-backs), whose
 // workgroups have lower indices here too.
 #include "contain.hpp"
+#include "crit.hpp"
 #include "frame.hpp"
+#include "graph.hpp"
 #include "join.hpp"
 #include "names.hpp"
 #include "overlap.hpp"
 #include "prep.hpp"
 #include "radix.hpp"
+#include "sol.hpp"
 #include "tilesort.hpp"
 #include "timeline.hpp"
+#include "waits.hpp"
 
 namespace hx {
 
 enum : int {
   LJ_INIT, LJ_PREP, LJ_TABLE, LJ_TSORT, LJ_TMERGE, LJ_HIST, LJ_PLAN, LJ_PASS, LJ_REFINE, LJ_STORE, LJ_RESOLVE, LJ_DUPS, LJ_FIX, LJ_EDGES, LJ_NAMES,
   LJ_NAMES_FOLD, LJ_OPNAMES, LJ_OPNAMES_FOLD, LJ_KERNEL_OPS, LJ_UNION, LJ_UNION_D, LJ_UNION_O, LJ_SEGOFF, LJ_SWEEP,
-  LJ_SWEEP_MANY, LJ_VBUILD, LJ_QUERY, LJ_DEPTH, LJ_OPAGG, LJ_NOCONTAIN
+  LJ_SWEEP_MANY, LJ_VBUILD, LJ_QUERY, LJ_DEPTH, LJ_OPAGG, LJ_NOCONTAIN,
+  LJ_DG_SCAN, LJ_WAITS, LJ_GRAPH, LJ_GRAPH_FOLD, LJ_SOL, LJ_SOL_FOLD, LJ_SOL_NAMES, LJ_CRIT_KERNELS, LJ_CRIT_HOST,
+  LJ_CRIT_LAST, LJ_CRIT_OPS, LJ_CRIT_ROWS, LJ_CRIT_LOCAL
 };
 constexpr int LV_SLICES = 8;
 
@@ -43,13 +49,24 @@ struct LevelArgs {
   LevelSlice s[LV_SLICES];
   int n;
   DevState* ds;
-  InitArgs init;
-  PrepArgs prep;
-  HistJobs hist;
-  union {  // one of them per launch
-    TileSortJobs tsort;
-    SortJobs sort;
-    RefineJobs refine;
+  union {
+    struct {  // up to the sorted lists
+      InitArgs init;
+      PrepArgs prep;
+      HistJobs hist;
+      union {  // one of them per launch
+        TileSortJobs tsort;
+        SortJobs sort;
+        RefineJobs refine;
+      };
+    };
+    struct {  // after them: the optional outputs
+      WaitsArgs waits;
+      GraphArgs graph;
+      SolArgs sol;
+      CritArgs crit;
+      int sol_blocks;
+    };
   };
   JoinArgs join;
   NamesArgs names;
@@ -171,8 +188,47 @@ __global__ __launch_bounds__(LV_THREADS) void k_level(LevelArgs) {
     case LJ_OPAGG:
       if (t < AG_THREADS) opagg_body(a.con, level_lds_as<OpaggLds>(lds), bx);
       break;
-    default:  // LJ_NOCONTAIN
+    case LJ_NOCONTAIN:
       if (t < 256) nocontain_body(a.opnames.keys[0], a.opnames.vals[0], a.ds, a.con.link, a.con.aux, bx, gx);
+      break;
+    case LJ_DG_SCAN:
+      if (t < DG_THREADS) dg_scan_body(a.waits, level_lds_as<DgScanLds>(lds), bx);
+      break;
+    case LJ_WAITS:
+      if (t < WT_THREADS) waits_body(a.waits, level_lds_as<WaitsLds>(lds), bx, gx);
+      break;
+    case LJ_GRAPH:
+      if (t < GR_THREADS) graph_body(a.graph, reinterpret_cast<unsigned long long*>(lds), bx, gx);
+      break;
+    case LJ_GRAPH_FOLD:
+      if (t < 256) graph_fold_body(a.graph, bx, by, gy);
+      break;
+    case LJ_SOL:
+      if (t < SOL_THREADS) sol_body(a.sol, reinterpret_cast<unsigned long long*>(lds), bx, gx);
+      break;
+    case LJ_SOL_FOLD:
+      if (t < 256) sol_fold_body(a.sol, a.sol_blocks, bx, by, gy);
+      break;
+    case LJ_SOL_NAMES:
+      if (t < 256) sol_names_body(a.sol, bx);
+      break;
+    case LJ_CRIT_KERNELS:
+      if (t < 256) crit_kernels_body(a.crit, level_lds_as<CritKernelsLds>(lds), bx, gx);
+      break;
+    case LJ_CRIT_HOST:
+      if (t < 256) crit_host_body(a.crit, level_lds_as<CritHostLds>(lds), bx, gx);
+      break;
+    case LJ_CRIT_LAST:
+      if (t < 256) crit_last_body(a.crit, bx, gx);
+      break;
+    case LJ_CRIT_OPS:
+      if (t < 256) crit_ops_body(a.crit, bx, gx);
+      break;
+    case LJ_CRIT_ROWS:
+      if (t < 256) crit_rows_body(a.crit, bx, gx);
+      break;
+    default:  // LJ_CRIT_LOCAL
+      if (t < CP_LT) crit_local_body(a.crit, level_lds_as<CritLocalLds>(lds), bx);
       break;
   }
 }
@@ -204,8 +260,8 @@ struct Level {
   }
 };
 
-// The whole call up to the per-op aggregates; the optional outputs' own
-// kernels and the last kernel follow on the same stream.
+// The whole call up to the critical path's walk; that and the last kernel
+// follow on the same stream.
 void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks, int passes) {
   LevelArgs a{};
   a.ds = c.ds;
@@ -288,6 +344,14 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
     l.launch();
   }
 
+  // the sorted lists are there
+  if (c.waits) a.waits = waits_args(c);
+  if (c.graph) a.graph = graph_args(c);
+  if (c.sol) {
+    a.sol = sol_args(c);
+    a.sol_blocks = c.sol_blocks;
+  }
+  if (c.crit) a.crit = crit_args(c);
   l.add(LJ_UNION, c.union_tiles, 1, UN_THREADS_SMALL, sizeof(UnionLds<UN_THREADS_SMALL>));
   if (c.contain) l.add(LJ_VBUILD, ct, 1, VB_THREADS, sizeof(VbuildLds));
   if (c.waits) {
@@ -303,6 +367,7 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
   if (c.contain) l.add(LJ_QUERY, ct, 1, QY_THREADS, sizeof(QueryLds));
   if (c.overlap) l.add(LJ_SEGOFF, segoff_blocks(c), 1, 256, 0);
   join_step();
+  if (c.waits) l.add(LJ_DG_SCAN, c.dg_tiles, 1, DG_THREADS, sizeof(DgScanLds));
   if (opn && a.opnames.lds) l.add(LJ_OPNAMES_FOLD, cdiv((int64_t)c.NOP * 4, 256), opnames_fold_rows(c), 256, 0);
   l.launch();
 
@@ -314,6 +379,7 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
   }
   if (c.contain) l.add(LJ_DEPTH, std::max<int64_t>(cdiv(c.sC.n_max, 256 * DP_ITEMS), 1), 1, 256, sizeof(DepthLds));
   join_step();
+  if (c.waits) l.add(LJ_WAITS, waits_blocks(c), 1, WT_THREADS, sizeof(WaitsLds));
   l.launch();
 
   if (c.contain) {
@@ -321,6 +387,30 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
     l.add(LJ_KERNEL_OPS, kernel_ops_blocks(c), 1, KO_THREADS, 0);
   }
   if (c.p.n_edges > 0) l.add(LJ_EDGES, std::min<int64_t>(cdiv(c.p.n_edges, 256), 1024), 1, 256, 0);
+  const int64_t cg = crit_grid(c.n);
+  if (c.crit && rows) {
+    l.add(LJ_CRIT_HOST, cg, 1, 256, sizeof(CritHostLds));
+    l.add(LJ_CRIT_KERNELS, cg, 1, 256, sizeof(CritKernelsLds));
+  }
+  if (c.graph) l.add(LJ_GRAPH, c.graph_blocks, 1, GR_THREADS, a.graph.lds ? (size_t)c.NG * GR_STATS * 8 : 0);
+  l.launch();
+
+  if (c.sol) l.add(LJ_SOL, c.sol_blocks, 1, SOL_THREADS, a.sol.lds ? (size_t)c.NOP * 32 : 0);
+  if (c.crit && rows) l.add(LJ_CRIT_LAST, cg, 1, 256, 0);
+  if (c.graph && a.graph.lds)
+    l.add(LJ_GRAPH_FOLD, cdiv((int64_t)c.NG * GR_STATS, 256), graph_fold_rows(c), 256, 0);
+  l.launch();
+
+  if (c.sol && a.sol.lds)
+    l.add(LJ_SOL_FOLD, cdiv((int64_t)c.NOP * 4, 256), std::min(SF_ROWS, c.sol_blocks), 256, 0);
+  if (c.crit && rows) {
+    l.add(LJ_CRIT_OPS, cg, 1, 256, 0);
+    l.add(LJ_CRIT_ROWS, cg, 1, 256, 0);
+  }
+  l.launch();
+
+  if (c.sol) l.add(LJ_SOL_NAMES, cdiv(c.NOP, 256), 1, 256, 0);
+  if (c.crit && rows) l.add(LJ_CRIT_LOCAL, cdiv(2 * c.n, CP_TE), 1, CP_LT, sizeof(CritLocalLds));
   l.launch();
 }
 
