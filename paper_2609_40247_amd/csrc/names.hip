@@ -27,7 +27,9 @@ __global__ __launch_bounds__(256) void k_opnames_fold(OpNamesArgs a) {
 
 int names_block_count(int64_t n_max, int NN) {
   if (NN > NM_LDS_NAMES) return (int)std::min<int64_t>(std::max<int64_t>(cdiv(n_max, 4096), 1), 1024);
-  return (int)std::min<int64_t>(std::max<int64_t>(cdiv(n_max, 8192), 1), 256);
+  // small windows: 4096 rows a workgroup, unless the tables get large
+  const int64_t b = std::max(NN <= 2048 ? cdiv(std::min(n_max, SMALL_ROWS), 4096) : 0, cdiv(n_max, 8192));
+  return (int)std::min<int64_t>(std::max<int64_t>(b, 1), 256);
 }
 
 void launch_names(Ctx& c) {
