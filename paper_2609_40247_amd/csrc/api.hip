@@ -460,7 +460,6 @@ static int enqueue_locked(Ctx& c, DeviceStreams* dsx) {
   stage_begin(c, HERSCHEL_STAGE_NAMES);
   launch_names(c);
   launch_names_reduce(c);
-  wait(c.st, 0);  // the op-name tables read the refined containment list
   launch_opnames(c);
   if (c.contain) {
     wait(c.st, 3);

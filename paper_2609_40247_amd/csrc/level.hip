@@ -189,7 +189,7 @@ __global__ __launch_bounds__(LV_THREADS) void k_level(LevelArgs) {
       if (t < AG_THREADS) opagg_body(a.con, level_lds_as<OpaggLds>(lds), bx);
       break;
     case LJ_NOCONTAIN:
-      if (t < 256) nocontain_body(a.opnames.keys[0], a.opnames.vals[0], a.ds, a.con.link, a.con.aux, bx, gx);
+      if (t < 256) nocontain_body(a.con.k[0], a.con.v[0], a.ds, a.con.link, a.con.aux, bx, gx);
       break;
     case LJ_DG_SCAN:
       if (t < DG_THREADS) dg_scan_body(a.waits, level_lds_as<DgScanLds>(lds), bx);
@@ -280,7 +280,7 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
   }
   a.sweep = sweep_args(c);
   a.con = contain_args(c);
-  const bool rows = c.n > 0, names = names_tables(c), fold = names && c.NN <= NM_LDS_NAMES, opn = opnames_wanted(c);
+  const bool rows = c.n > 0, names = names_wanted(c), fold = names && c.NN <= NM_LDS_NAMES, opn = opnames_wanted(c);
   const int64_t ct = std::max<int64_t>(cdiv(c.sC.n_max, CT_TILE), 1);
   Level l(c, a);
   // The join's steps, one a launch from the emptied table on (its list is
@@ -306,7 +306,13 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
   }
   // the sorts, the names' tables and the first steps of the join
   const size_t names_lds = c.NN <= NM_LDS_NAMES ? (size_t)c.NN * 32 : 0;
+  auto tables = [&]() {
+    if (names) l.add(LJ_NAMES, c.name_blocks, 1, NM_THREADS, names_lds);
+    if (opn && rows) l.add(LJ_OPNAMES, c.opn_blocks, 1, ON_THREADS, a.opnames.lds ? (size_t)c.NOP * 32 : 0);
+  };
   auto names_fold = [&]() {
+    if (opn && rows && a.opnames.lds)
+      l.add(LJ_OPNAMES_FOLD, cdiv((int64_t)c.NOP * 4, 256), opnames_fold_rows(c), 256, 0);
     if (fold) l.add(LJ_NAMES_FOLD, cdiv((int64_t)c.NN * 4, 256), names_fold_rows(c), 256, 0);
   };
   if (c.n <= TS_ROWS) {
@@ -315,7 +321,7 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
     l.add(LJ_TSORT, sort_grid, 1, TS_THREADS, sizeof(TileSortLds));
     l.add(LJ_TABLE, std::min<int64_t>(cdiv(2 * std::max<int64_t>(c.n, 1), HIST_CHUNK), HIST_MAX_BLOCKS), 1,
           HIST_THREADS, sizeof(JtEmptyLds));
-    if (names) l.add(LJ_NAMES, c.name_blocks, 1, NM_THREADS, names_lds);
+    tables();
     l.launch();
     l.add(LJ_TMERGE, merge_grid, 1, TM_THREADS, sizeof(TileMergeLds));
     join_step();
@@ -323,7 +329,7 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
     l.launch();
   } else {
     l.add(LJ_HIST, hist_grid, hist_m + 1, HIST_THREADS, sizeof(DigitHistLds));
-    if (names) l.add(LJ_NAMES, c.name_blocks, 1, NM_THREADS, names_lds);
+    tables();
     l.launch();
     l.add(LJ_PLAN, hist_nd, hist_m, PLAN_THREADS, sizeof(HistPlanLds));
     join_step();
@@ -359,7 +365,6 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
     l.add(LJ_UNION_O, c.union_tiles, 1, UN_THREADS_SMALL, sizeof(UnionLds<UN_THREADS_SMALL>));
   }
   join_step();
-  if (opn) l.add(LJ_OPNAMES, c.opn_blocks, 1, ON_THREADS, a.opnames.lds ? (size_t)c.NOP * 32 : 0);
   if (!c.contain && (c.o.link || c.o.aux))
     l.add(LJ_NOCONTAIN, std::min<int64_t>(std::max<int64_t>(cdiv(c.n, 256 * 8), 1), 2048), 1, 256, 0);
   l.launch();
@@ -368,7 +373,6 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
   if (c.overlap) l.add(LJ_SEGOFF, segoff_blocks(c), 1, 256, 0);
   join_step();
   if (c.waits) l.add(LJ_DG_SCAN, c.dg_tiles, 1, DG_THREADS, sizeof(DgScanLds));
-  if (opn && a.opnames.lds) l.add(LJ_OPNAMES_FOLD, cdiv((int64_t)c.NOP * 4, 256), opnames_fold_rows(c), 256, 0);
   l.launch();
 
   if (c.overlap) {

@@ -33,7 +33,7 @@ int names_block_count(int64_t n_max, int NN) {
 }
 
 void launch_names(Ctx& c) {
-  if (!names_tables(c)) return;
+  if (!names_wanted(c)) return;
   NamesArgs a = names_args(c);
   const size_t lds = c.NN <= NM_LDS_NAMES ? (size_t)c.NN * 32 : 0;
   hipLaunchKernelGGL(k_names_partial, dim3(c.name_blocks), dim3(NM_THREADS), lds, c.st, a);
@@ -47,7 +47,7 @@ void launch_kernel_ops(Ctx& c) {
 }
 
 void launch_names_reduce(Ctx& c) {
-  if (c.NN > NM_LDS_NAMES || !names_tables(c)) return;
+  if (c.NN > NM_LDS_NAMES || !names_wanted(c)) return;
   NamesArgs a = names_args(c);
   hipLaunchKernelGGL(k_names_reduce, dim3((unsigned)cdiv((int64_t)c.NN * 4, 256), (unsigned)names_fold_rows(c)), dim3(256),
                      0, c.st, a);
@@ -62,7 +62,7 @@ int opnames_block_count(int64_t n_max, int NOP) {
 }
 
 void launch_opnames(Ctx& c) {
-  if (!opnames_wanted(c)) return;
+  if (!opnames_wanted(c) || c.n == 0) return;
   const OpNamesArgs a = opnames_args(c);
   hipLaunchKernelGGL(k_opnames_partial, dim3((unsigned)c.opn_blocks), dim3(ON_THREADS),
                      a.lds ? (size_t)c.NOP * 32 : 0, c.st, a);

@@ -33,6 +33,7 @@ struct PrepArgs {
   int sb, tb, wb;
   int64_t n_tiles;
   bool jt_range;  // find each process's id range (at most JT_PROCS processes)
+  bool c_list;    // the containment list is wanted
   bool waits;     // the op-name list and device-lane keys (idle coincidence)
   int nob;        // bits of an op name
   bool sol;       // ops carry operation counts and bytes (operator efficiency), which must be >= 0
@@ -291,7 +292,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a, PrepLds<ITEMS>& lds
         }
       }
     }
-    if (fl & (2u << (4 * j))) {
+    if (a.c_list && (fl & (2u << (4 * j)))) {
       const uint64_t pos = s_base[1] + s_off[j][wv][1] + popc(s_bal[j][wv][1] & lt);
       if (in_range(a.ds, (int64_t)pos, a.n)) {
         a.kC[pos] = kA[j];
@@ -332,6 +333,7 @@ static inline PrepArgs prep_args(const Ctx& c) {
   a.wb = c.wb;
   a.n_tiles = c.prep_tiles;
   a.jt_range = c.P <= JT_PROCS;
+  a.c_list = c.contain || c.o.link || c.o.aux;
   a.waits = c.waits;
   a.nob = c.nob;
   a.sol = c.sol;
