@@ -236,16 +236,18 @@ __device__ __forceinline__ void jt_resolve_body(const JoinArgs& a, JtResolveLds&
     lw[u] = a.L[sc];
     kw[u] = a.K[sc];
   }
-  // round 3: times (a launch that joins a kernel: the kernel's start and end
-  // and its own start; a kernel with edges: its start and end)
+  // round 3: times (a launch that joins a kernel: the kernel's start, its own
+  // start, and with containment the kernel's end; a kernel with edges: its
+  // start and end; the others read row 0's, one line for all of them)
+  const bool ends = a.contain || a.kmax;
   int64_t t0[IT], t1[IT], t2[IT];
 #pragma unroll
   for (int u = 0; u < IT; ++u) {
     const bool kern = (key[u] & 1) != 0;
     const bool joins = !kern && slot[u] >= 0 && lw[u] == row[u] && kw[u] != JT_EMPTY;
-    const uint32_t kr = kern ? row[u] : joins ? kw[u] : 0u;
+    const uint32_t kr = kern ? (a.kmax ? row[u] : 0u) : joins ? kw[u] : 0u;
     t0[u] = a.ts[kr];
-    t1[u] = a.te[kr];
+    t1[u] = ends ? a.te[kr] : 0;
     t2[u] = a.ts[joins ? row[u] : 0u];
   }
   uint64_t fb[IT];    // the wave's lanes whose item u goes to the fix-up list

@@ -198,11 +198,11 @@ static inline NamesArgs names_args(const Ctx& c) {
 // records of one kind together, so a wave without ops reads only the kinds,
 // and one with ops reads their columns coalesced (from the sorted containment
 // list the same columns were gathered: 13.5 us on the decode-step trace
-// against 12.5, 19 against 13.6 on a
-// window of the batch, 29 against 18 on the prefill/decode trace).  It waits for no list,
-// and without containment prep need not write that list.  A private LDS table
-// per workgroup, written out whole and folded by a second kernel; more op
-// names than the LDS budget go to the outputs by global atomics.
+// against 12.5, 19 against 13.6 on a window of the batch, 29 against 18 on
+// the prefill/decode trace).  It waits for no list, and without containment
+// prep need not write that list.  A private LDS table per workgroup, written
+// out whole and folded by a second kernel; more op names than the LDS budget
+// go to the outputs by global atomics.
 constexpr int ON_THREADS = 512;
 constexpr int ON_LDS_NAMES = 2048;  // 64 KB of LDS, the default dynamic limit
 constexpr int ON_MAX_BLOCKS = 512;
