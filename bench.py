@@ -33,8 +33,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 METRIC = "trace events analyzed/sec (M ev/s) at 1 MI355X + achieved HBM GB/s % peak"
 HBM_PEAK_GBS = 8000.0
 ROOFLINE_STAGE = "sort"
-ROOFLINE_KERNEL = "k_radix_pass"
-BYTES_PER_KEY_PASS = 24  # a digit pass reads and writes one 8-byte key and one 4-byte row index
+ROOFLINE_KERNEL = "k_radix_pass_packed"
+BYTES_PER_KEY_PASS = 16  # a digit pass reads and writes one 8-byte word (key above row)
 CSRC = os.path.join(ROOT, "paper_2609_40247_amd", "csrc")
 
 WORKLOADS = {
@@ -413,7 +413,7 @@ def main() -> int:
             H.herschel_time_stage(sid, None, None)
             print(f"stage {name:14s} {tot / 5 * 1e3:9.1f} us", file=sys.stderr)
 
-    # per launch of k_radix_pass: the stage's bytes and time over its launches
+    # per launch of the digit pass: the stage's bytes and time over its launches
     alg = BYTES_PER_KEY_PASS * units / launches
     launch_s = stage_ms * 1e-3 / launches
     achieved = alg / launch_s / 1e9

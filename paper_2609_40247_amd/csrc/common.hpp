@@ -61,6 +61,22 @@ constexpr uint64_t JK_CORR_MASK = (1ull << 51) - 1;
 constexpr uint32_t JT_EMPTY = ~0u;
 constexpr uint64_t SIGN64 = 1ull << 63;
 
+// A packed sort word: a key without its lowest `drop` bits above its row.
+// The bits dropped (none where key and row fit in 64 bits) are time bits,
+// which the refine pass reads again from the row; a containment key that
+// loses bits keeps its lowest, the launch bit, between the two.
+struct PackFmt {
+  int row_bits;
+  int drop;
+  int keep;  // 1: the key's lowest bit is kept
+  __host__ __device__ __forceinline__ int key_shift() const { return row_bits + keep; }  // where the key begins
+  __device__ __forceinline__ uint32_t row(uint64_t w) const { return (uint32_t)w & ((1u << row_bits) - 1u); }
+  __device__ __forceinline__ uint64_t pack(uint64_t key, uint32_t r) const {
+    return ((key >> drop) << key_shift()) | ((key & (uint64_t)keep) << row_bits) | r;
+  }
+};
+static_assert(HERSCHEL_MAX_ROWS <= (1ll << 30), "a row fits in row_bits <= 30");
+
 // Per-call device state, zeroed by the init kernel.
 struct DevState {
   uint32_t ticket[N_TICKETS];

@@ -80,6 +80,8 @@ struct CritArgs {
   const int32_t* link;
   const int32_t* aux;
   const uint32_t* k_rows;  // admitted kernels in row order
+  bool packed;             // ... as packed words
+  PackFmt pkE;
   uint64_t* eK;            // the kernel-end list before its sort
   uint32_t* eV;
   int32_t* pred;  // [2n] release of each event (-1 none)
@@ -178,8 +180,9 @@ __device__ __forceinline__ void crit_elist_body(const CritArgs& a, uint32_t bx, 
   const int64_t cnt = a.ds->nK;
   for (int64_t i = (int64_t)bx * 256 + threadIdx.x; i < cnt; i += (int64_t)gx * 256) {
     const uint32_t r = a.k_rows[i];
-    a.eK[i] = ((uint64_t)a.pid[r] << a.wb1) | (uint64_t)(cp_end(a, r) - a.W0);
-    a.eV[i] = r;
+    const uint64_t k = ((uint64_t)a.pid[r] << a.wb1) | (uint64_t)(cp_end(a, r) - a.W0);
+    a.eK[i] = a.packed ? a.pkE.pack(k, r) : k;
+    if (!a.packed) a.eV[i] = r;
   }
 }
 
@@ -699,6 +702,8 @@ static inline CritArgs crit_args(const Ctx& c) {
   a.link = c.o.link;
   a.aux = c.o.aux;
   a.k_rows = c.k_rows;
+  a.packed = c.packed;
+  a.pkE = c.sE.pk;
   a.eK = c.sE.k[0];
   a.eV = c.sE.v[0];
   a.pred = c.crit_pred;

@@ -21,6 +21,8 @@ struct SortBufs {
   int id = 0;                           // sort index: histogram, parity
   int first = 0;                        // first digit sorted by passes (1: digit 0 left to the refine pass)
   int sh1 = 8;                          // lowest bit of digit 1 (digit d >= 1 is bits sh1 + 8(d-1) ..)
+  int key_bits = 0;
+  PackFmt pk{};                         // its packed words (Ctx::packed)
 };
 
 // Digits of a key_bits-bit sort key.  With `refine` (keys wider than 32
@@ -66,6 +68,7 @@ struct Ctx {
   int64_t W0 = 0, W1 = 0, W = 0, thr = 0;
   int P = 0, S = 0, T = 0, NN = 0, NOP = 0;
   bool small = false;  // launched level by level
+  bool packed = false;  // the sorts move packed words (PackFmt)
   bool contain = false, overlap = false, waits = false, sol = false, crit = false, graph = false;
   int NG = 0;                          // graph nodes (graph replay separation)
   int nob = 0;                         // bits of an op name (idle coincidence)
@@ -239,6 +242,7 @@ constexpr int RS_ITEMS = 8;
 constexpr int RS_TILE = RS_THREADS * RS_ITEMS;  // 4096 keys per tile
 constexpr int RS_LB_WORDS = 512;                // look-back words per tile: 256 counts, 256 window sums
 constexpr int RS_WAVES_PER_EU = 6;              // three workgroups of 8 waves per CU
+constexpr int RS_PK_WAVES_PER_EU = 8;           // packed words: four
 // Keys wider than 32 bits leave their lowest digit to the refine pass, which
 // orders the runs of keys equal above it; runs up to RF_SHORT are fixed in
 // place, longer ones listed.

@@ -48,6 +48,7 @@ struct LevelSlice {
 struct LevelArgs {
   LevelSlice s[LV_SLICES];
   int n;
+  bool packed;  // the sorts move packed words
   DevState* ds;
   union {
     struct {  // up to the sorted lists
@@ -121,10 +122,18 @@ __global__ __launch_bounds__(LV_THREADS) void k_level(LevelArgs) {
       if (t < PLAN_THREADS) hist_plan_body(a.hist, a.ds, level_lds_as<HistPlanLds>(lds), bx, by);
       break;
     case LJ_PASS:
-      if (t < RS_THREADS) radix_pass_body(a.sort, a.ds, level_lds_as<RadixPassLds>(lds), bx);
+      if (t >= RS_THREADS) break;
+      if (a.packed)
+        radix_pass_body<true>(a.sort, a.ds, level_lds_as<RadixPassLds<true>>(lds), bx);
+      else
+        radix_pass_body<false>(a.sort, a.ds, level_lds_as<RadixPassLds<false>>(lds), bx);
       break;
     case LJ_REFINE:
-      if (t < RF_THREADS) refine_body(a.refine, a.ds, level_lds_as<RefineLds>(lds), bx, by);
+      if (t >= RF_THREADS) break;
+      if (a.packed)
+        refine_body<true>(a.refine, a.ds, level_lds_as<RefineLds>(lds), bx, by);
+      else
+        refine_body<false>(a.refine, a.ds, level_lds_as<RefineLds>(lds), bx, by);
       break;
     case LJ_STORE:
       if (t < 256) jt_store_body<1>(a.join, bx);
@@ -265,6 +274,7 @@ struct Level {
 void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks, int passes) {
   LevelArgs a{};
   a.ds = c.ds;
+  a.packed = c.packed;
   a.init = init_args(c);
   a.prep = prep_args(c);
   int64_t hist_grid;
@@ -337,8 +347,9 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
     l.launch();
     for (int p = 0; p < passes; ++p) {
       int64_t grid;
-      a.sort = sort_jobs(ss, cc, ks, p, &grid);
-      if (a.sort.m > 0) l.add(LJ_PASS, grid, 1, RS_THREADS, sizeof(RadixPassLds));
+      a.sort = sort_jobs(c, ss, cc, ks, p, &grid);
+      if (a.sort.m > 0)
+        l.add(LJ_PASS, grid, 1, RS_THREADS, c.packed ? sizeof(RadixPassLds<true>) : sizeof(RadixPassLds<false>));
       join_step();
       l.launch();
     }

@@ -34,6 +34,9 @@ struct PrepArgs {
   int64_t n_tiles;
   bool jt_range;  // find each process's id range (at most JT_PROCS processes)
   bool c_list;    // the containment list is wanted
+  bool packed;    // the sorts' lists are packed words (the containment list: if sorted)
+  bool packed_c;
+  PackFmt pkK, pkC, pkD, pkO;
   bool waits;     // the op-name list and device-lane keys (idle coincidence)
   int nob;        // bits of an op name
   bool sol;       // ops carry operation counts and bytes (operator efficiency), which must be >= 0
@@ -283,20 +286,21 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a, PrepLds<ITEMS>& lds
     if (fl & (1u << (4 * j))) {
       const uint64_t pos = s_base[0] + s_off[j][wv][0] + popc(s_bal[j][wv][0] & lt);
       if (in_range(a.ds, (int64_t)pos, a.n)) {
-        a.kK[pos] = kA[j];
-        a.vK[pos] = r;
+        a.kK[pos] = a.packed ? a.pkK.pack(kA[j], r) : kA[j];
+        if (!a.packed) a.vK[pos] = r;
         a.kRows[pos] = r;
         if (a.waits) {  // the device lane: the timeline key without its stream
-          a.kD[pos] = ((kA[j] >> (a.sb + a.wb)) << a.wb) | (kA[j] & ((1ull << a.wb) - 1));
-          a.vD[pos] = r;
+          const uint64_t kd = ((kA[j] >> (a.sb + a.wb)) << a.wb) | (kA[j] & ((1ull << a.wb) - 1));
+          a.kD[pos] = a.packed ? a.pkD.pack(kd, r) : kd;
+          if (!a.packed) a.vD[pos] = r;
         }
       }
     }
     if (a.c_list && (fl & (2u << (4 * j)))) {
       const uint64_t pos = s_base[1] + s_off[j][wv][1] + popc(s_bal[j][wv][1] & lt);
       if (in_range(a.ds, (int64_t)pos, a.n)) {
-        a.kC[pos] = kA[j];
-        a.vC[pos] = r;
+        a.kC[pos] = a.packed_c ? a.pkC.pack(kA[j], r) : kA[j];
+        if (!a.packed_c) a.vC[pos] = r;
       }
     }
     if (fl & (4u << (4 * j))) {
@@ -309,8 +313,8 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a, PrepLds<ITEMS>& lds
     if (fl & (8u << (4 * j))) {
       const uint64_t pos = s_base[3] + s_off[j][wv][3] + popc(s_bal[j][wv][3] & lt);
       if (in_range(a.ds, (int64_t)pos, a.n)) {
-        a.kO[pos] = kB[j];
-        a.vO[pos] = r;
+        a.kO[pos] = a.packed ? a.pkO.pack(kB[j], r) : kB[j];
+        if (!a.packed) a.vO[pos] = r;
       }
     }
   }
@@ -334,6 +338,12 @@ static inline PrepArgs prep_args(const Ctx& c) {
   a.n_tiles = c.prep_tiles;
   a.jt_range = c.P <= JT_PROCS;
   a.c_list = c.contain || c.o.link || c.o.aux;
+  a.packed = c.packed;
+  a.packed_c = c.packed && c.contain;
+  a.pkK = c.sK.pk;
+  a.pkC = c.sC.pk;
+  a.pkD = c.sD.pk;
+  a.pkO = c.sO.pk;
   a.waits = c.waits;
   a.nob = c.nob;
   a.sol = c.sol;

@@ -1,6 +1,18 @@
-// LSD radix sort of 64-bit keys (optionally with a 32-bit payload) for CDNA4.
+// LSD radix sort of 64-bit keys with 32-bit rows for CDNA4.
 //
-// One launch per 8-bit digit, shared by the independent sorts of a call.  Each workgroup ranks a tile of 4096 keys with
+// One launch per 8-bit digit, shared by the independent sorts of a call.
+// What the passes move is, where it can be, one 64-bit word per element
+// (PackFmt: the key above its row, without the key's lowest time bits if
+// both are more than 64 bits), and the refine pass makes keys and rows of
+// them.  A pass is bound by the bytes it moves and by how many tiles share a
+// CU: 16 bytes per element instead of 24 and four tiles instead of three took
+// it from 25.1 to 21.9 us for 3.0M rows (decode steps, one process), from 199
+// to 128 us for 24M (eight processes), while the refine pass, which then writes
+// every element, grew from 24.5 to 26.9 us and from 82 to 126 us.  (A word always
+// without its lowest bits, every time gathered: 715 -> 735 us a call of 3.0M
+// shuffled rows, against 704 with the bits kept where they fit.)
+//
+// Each workgroup ranks a tile of 4096 keys with
 // wave64 ballots (a 64-lane match of the digit built from 8 ballots gives the
 // rank among equal digits in one step), publishes its 256 per-digit counts
 // through a decoupled look-back (one chain per digit, two lanes per digit),
@@ -352,10 +364,11 @@ struct SortJobs {
 };
 
 // One digit pass of up to N_SORTS independent sorts (each on its own digit).
-// 512 threads rank a tile of 4096 keys; the tile (48 KB) and the per-wave
-// digit counts (8 KB, in the key area until the keys are placed) keep the
-// LDS of a workgroup under a third of the CU's (with the allocation
-// granularity), so three tiles share a CU.
+// 512 threads rank a tile of 4096 keys; the tile (32 KB of packed words, 48
+// KB of keys and rows) and the per-wave digit counts (8 KB, in the key area
+// until the keys are placed) keep the LDS of a workgroup under a fourth of the
+// CU's, of keys and rows a third (with the allocation granularity), so four
+// or three tiles share a CU.
 //
 // The grid is one-dimensional and sized for every sort's largest input.
 // The tiles whose digit moves data are numbered sort after sort, and
@@ -374,16 +387,19 @@ constexpr int RS_NW = RS_THREADS / WAVE;  // waves per workgroup
 constexpr int RS_NSL = RS_THREADS / 256;  // look-back slices per digit
 constexpr int RS_LB_WIN = 16;             // positions polled per slice and round trip
 
+template <bool PACKED>
 struct RadixPassLds {
   uint64_t s_key[RS_TILE];
-  uint32_t s_val[RS_TILE];
+  uint32_t s_val[PACKED ? 256 : RS_TILE];  // rows (packed words hold them); first the tile's digit counts
   uint32_t s_local[256];
   uint32_t s_scan[RS_NW];
   uint32_t s_lb_sum[RS_NSL][256];
   uint8_t s_lb_state[RS_NSL][256];
 };
 
-__device__ __forceinline__ void radix_pass_body(const SortJobs& jobs, DevState* ds, RadixPassLds& lds, uint32_t bx) {
+template <bool PACKED>
+__device__ __forceinline__ void radix_pass_body(const SortJobs& jobs, DevState* ds, RadixPassLds<PACKED>& lds,
+                                                uint32_t bx) {
   constexpr int NW = RS_NW, NSL = RS_NSL, LB_WIN = RS_LB_WIN;
   auto& s_key = lds.s_key;
   auto& s_val = lds.s_val;
@@ -431,7 +447,9 @@ __device__ __forceinline__ void radix_pass_body(const SortJobs& jobs, DevState* 
     if (b < tiles && jb.d + 1 < jb.nd && !((tr[i] >> (jb.d + 1)) & 1) && tid < RS_LB_WORDS)
       jb.status1[((int64_t)(jb.d - jb.first) * jb.tiles_max + b) * RS_LB_WORDS + tid] = 0u;
     if (jb.d == jb.first && b == 0 && tid == 0)
-      ds->sort_parity[jb.id] = (uint32_t)(popc(~tr[i] & ((jb.nd >= 32 ? 0u : 1u << jb.nd) - 1u)) & 1);
+      // (the refine pass moves packed words once more)
+      ds->sort_parity[jb.id] =
+          (uint32_t)(popc(~tr[i] & ((jb.nd >= 32 ? 0u : 1u << jb.nd) - 1u)) + (PACKED ? 1 : 0)) & 1u;
     nt[i] = ((tr[i] >> jb.d) & 1) ? 0u : tiles;
   }
   int sel = -1;
@@ -482,7 +500,7 @@ __device__ __forceinline__ void radix_pass_body(const SortJobs& jobs, DevState* 
   for (int j = 0; j < RS_ITEMS; ++j) {
     const uint32_t idx = min(wbase + j * WAVE, n - 1);
     key[j] = kin[idx];
-    val[j] = vin[idx];
+    val[j] = PACKED ? 0u : vin[idx];
   }
   // the counters are cleared while the loads are in flight; the tile's
   // digit counts sit in the row area until the rows are placed
@@ -572,7 +590,7 @@ __device__ __forceinline__ void radix_pass_body(const SortJobs& jobs, DevState* 
   for (int j = 0; j < RS_ITEMS; ++j) {
     if (digit_of(j) < 256 && in_range(ds, rank[j], RS_TILE)) {
       s_key[rank[j]] = key[j];
-      s_val[rank[j]] = val[j];
+      if (!PACKED) s_val[rank[j]] = val[j];
     }
   }
 
@@ -679,7 +697,7 @@ __device__ __forceinline__ void radix_pass_body(const SortJobs& jobs, DevState* 
     const uint32_t gpos = s_glob[dg] + (i - s_local[dg]);
     if (in_bounds(ds, gpos, n)) {
       kout[gpos] = kk;
-      vout[gpos] = s_val[i];
+      if (!PACKED) vout[gpos] = s_val[i];
     }
   }
 }
@@ -703,11 +721,32 @@ struct RefineJob {
   int contain;   // 1: containment tie rule
   int slot;      // list index (the sort's id)
   int shift;     // runs are keys equal above this bit (the passes' lowest, or 0 when every digit was sorted)
+  int base;      // the shift in what the passes moved
+  PackFmt pk;    // ... if that is packed words
+  int pid_shift; // bits of a key below its process
+  int ends;      // 1: the key's time is the record's end, clipped at W1
 };
 struct RefineJobs {
   RefineJob j[N_SORTS];
+  const int64_t* ts;
   const int64_t* te;
+  const int64_t* off;
+  int64_t W0, W1;
 };
+
+// The whole key of a packed word that lost bits, of a row with time t.
+__device__ __forceinline__ uint64_t rf_rebuild(const RefineJobs& jobs, const RefineJob& jb, uint64_t w, int64_t t) {
+  const uint64_t hi = w >> jb.pk.key_shift();
+  if (jobs.off) t -= jobs.off[(int32_t)(hi >> (jb.pid_shift - jb.pk.drop))];
+  if (jb.ends) t = t < jobs.W1 ? t : jobs.W1;
+  uint64_t low = (uint64_t)(t - jobs.W0);
+  if (jb.pk.keep) low = (low << 1) | ((w >> jb.pk.row_bits) & 1);
+  return (hi << jb.pk.drop) | (low & ((1ull << jb.pk.drop) - 1));
+}
+__device__ __forceinline__ uint64_t rf_unpack(const RefineJobs& jobs, const RefineJob& jb, uint64_t w) {
+  if (jb.pk.drop == 0) return w >> jb.pk.key_shift();
+  return rf_rebuild(jobs, jb, w, (jb.ends ? jobs.te : jobs.ts)[jb.pk.row(w)]);
+}
 
 // a before b in the refined order (a and b from one run)
 __device__ __forceinline__ bool rf_before(const RefineJob& jb, const int64_t* te, uint64_t ka, uint32_t ra, uint64_t kb,
@@ -726,30 +765,34 @@ constexpr int RF_TILE = RF_THREADS * RF_ITEMS;  // positions whose runs a workgr
 constexpr int RF_SPAN = 1 + RF_TILE + RF_SHORT;  // the position before the tile, the tile, and its runs' reach
 
 // One long run (more than RF_SHORT keys, starting at position p), sorted by
-// the whole workgroup: the run is copied into the sort's other buffer (free
-// once the passes are done) at the same positions, sorted there by a
-// bitonic network that only compares pairs inside the run (the positions
-// past its end act as +infinity, and every comparator puts the smaller
-// element first), and copied back.  Only the high part of the run's keys
-// (above the shift) is read by other workgroups meanwhile, and it is the
-// same for every key of the run.
-__device__ void refine_long_run(const RefineJob& jb, const int64_t* te, uint64_t* keys, uint32_t* vals, uint64_t* sk,
-                                uint32_t* sv, int64_t p, int64_t n, int64_t* s_len) {
-  const uint64_t hi = keys[p] >> jb.shift;
+// the whole workgroup with a bitonic network that only compares pairs inside
+// the run (the positions past its end act as +infinity, and every comparator
+// puts the smaller element first).  The network works in the buffer that
+// holds nothing anybody reads (the passes are done) at the run's own
+// positions: packed words are rebuilt into the result's buffer, which is that
+// one; otherwise keys and rows are copied to the other buffer and back.  Only
+// the high part of the run's keys (above the shift) is read by other
+// workgroups meanwhile, and it is the same for every key of the run.
+template <bool PACKED>
+__device__ void refine_long_run(const RefineJobs& jobs, const RefineJob& jb, uint64_t* keys, uint32_t* vals,
+                                uint64_t* sk, uint32_t* sv, int64_t p, int64_t n, int64_t* s_len) {
+  const int sh = jb.base;
+  const uint64_t hi = keys[p] >> sh;
   if (threadIdx.x == 0) *s_len = n - p;
   __syncthreads();
   // the run's end: the first position past it, found RF_THREADS at a time
   for (int64_t b = p; b < n; b += RF_THREADS) {
     const int64_t i = b + threadIdx.x;
-    if (i < n && (keys[i] >> jb.shift) != hi) atomicMin((unsigned long long*)s_len, (unsigned long long)(i - p));
+    if (i < n && (keys[i] >> sh) != hi) atomicMin((unsigned long long*)s_len, (unsigned long long)(i - p));
     __syncthreads();
     if (*s_len < n - p) break;
     __syncthreads();
   }
   const int64_t len = *s_len;
   for (int64_t i = threadIdx.x; i < len; i += RF_THREADS) {
-    sk[p + i] = keys[p + i];
-    sv[p + i] = vals[p + i];
+    const uint64_t k = keys[p + i];
+    sk[p + i] = PACKED ? rf_unpack(jobs, jb, k) : k;
+    sv[p + i] = PACKED ? jb.pk.row(k) : vals[p + i];
   }
   __syncthreads();
   int64_t m = 1;
@@ -762,7 +805,7 @@ __device__ void refine_long_run(const RefineJob& jb, const int64_t* te, uint64_t
         if (l > i && l < len) {
           const uint64_t ki = sk[p + i], kl = sk[p + l];
           const uint32_t ri = sv[p + i], rl = sv[p + l];
-          if (rf_before(jb, te, kl, rl, ki, ri)) {
+          if (rf_before(jb, jobs.te, kl, rl, ki, ri)) {
             sk[p + i] = kl;
             sv[p + i] = rl;
             sk[p + l] = ki;
@@ -773,6 +816,7 @@ __device__ void refine_long_run(const RefineJob& jb, const int64_t* te, uint64_t
       __syncthreads();
     }
   }
+  if (PACKED) return;
   for (int64_t i = threadIdx.x; i < len; i += RF_THREADS) {
     keys[p + i] = sk[p + i];
     vals[p + i] = sv[p + i];
@@ -784,13 +828,18 @@ __device__ void refine_long_run(const RefineJob& jb, const int64_t* te, uint64_t
 // position before the tile and the RF_SHORT after it, and finds the tile's
 // run starts there.  A thread per run orders it in LDS (insertion sort:
 // the runs are short, and many are in order already) and marks the
-// positions that moved; the workgroup then writes those back, coalesced.
-// A run longer than RF_SHORT (rare) is noted, and the workgroup sorts it
-// afterwards in the sort's other buffer.
+// positions to write; the workgroup then writes those, coalesced.  A run
+// longer than RF_SHORT (rare) is noted, and the workgroup sorts it
+// afterwards.
+//
+// Of keys and rows, the positions that moved are written back in place.
+// Packed words become keys and rows here (of keys that lost bits each row's
+// time is gathered), and every position is written, to the other buffer, by the tile
+// that its run starts in: neighbouring tiles still read the words.
 struct RefineLds {
   uint64_t s_k[RF_SPAN];
   uint32_t s_v[RF_SPAN];
-  uint8_t s_chg[RF_SPAN];       // 1: the position moved
+  uint8_t s_chg[RF_SPAN];       // 1: the position is to be written
   int32_t s_run[RF_TILE / 2];  // span indices of the tile's run starts (a run has two keys or more)
   int s_nrun;
   int64_t s_long[RF_TILE / (RF_SHORT + 1) + 1];  // positions of the tile's long runs
@@ -798,6 +847,7 @@ struct RefineLds {
   int64_t s_len;
 };
 
+template <bool PACKED>
 __device__ __forceinline__ void refine_body(const RefineJobs& jobs, DevState* ds, RefineLds& lds, uint32_t bx,
                                             uint32_t by) {
   auto& s_k = lds.s_k;
@@ -811,8 +861,24 @@ __device__ __forceinline__ void refine_body(const RefineJobs& jobs, DevState* ds
   const RefineJob& jb = jobs.j[by];
   const int64_t n = *jb.count;
   const int64_t t0 = (int64_t)bx * RF_TILE;
-  if (n < 2 || t0 >= n) return;
-  const int par = (int)ds->sort_parity[jb.id];
+  if (n < (PACKED ? 1 : 2) || t0 >= n) return;
+  const int res = (int)ds->sort_parity[jb.id];  // the result's buffer
+  const int par = PACKED ? res ^ 1 : res;       // the passes' last
+  if (PACKED && (ds->status & DS_LOGIC)) {
+    // the passes stopped short: the rows in any order, so that what follows
+    // reads rows (the call reports the error)
+    for (int64_t p = t0 + threadIdx.x; p < min<int64_t>(n, t0 + RF_TILE); p += RF_THREADS) {
+      const uint64_t w = jb.k[0][p];
+      if (res == 1) {
+        jb.k[1][p] = rf_unpack(jobs, jb, w);
+        jb.v[1][p] = jb.pk.row(w);
+      } else {
+        jb.k[0][p] = rf_unpack(jobs, jb, w);
+        jb.v[0][p] = jb.pk.row(w);
+      }
+    }
+    return;
+  }
   uint64_t* keys = jb.k[par];
   uint32_t* vals = jb.v[par];
   if (threadIdx.x == 0) {
@@ -830,7 +896,22 @@ __device__ __forceinline__ void refine_body(const RefineJobs& jobs, DevState* ds
     int64_t q = t0 - 1 + i;
     q = q < 0 ? 0 : q >= n ? n - 1 : q;
     lk[u] = keys[q];
-    lv[u] = vals[q];
+    lv[u] = PACKED ? 0u : vals[q];
+  }
+  if (PACKED) {
+#pragma unroll
+    for (int u = 0; u < RF_LD; ++u) lv[u] = jb.pk.row(lk[u]);
+    if (jb.pk.drop == 0) {
+#pragma unroll
+      for (int u = 0; u < RF_LD; ++u) lk[u] >>= jb.pk.key_shift();
+    } else {
+      const int64_t* tcol = jb.ends ? jobs.te : jobs.ts;
+      int64_t t[RF_LD];
+#pragma unroll
+      for (int u = 0; u < RF_LD; ++u) t[u] = tcol[lv[u]];
+#pragma unroll
+      for (int u = 0; u < RF_LD; ++u) lk[u] = rf_rebuild(jobs, jb, lk[u], t[u]);
+    }
   }
 #pragma unroll
   for (int u = 0; u < RF_LD; ++u) {
@@ -847,7 +928,9 @@ __device__ __forceinline__ void refine_body(const RefineJobs& jobs, DevState* ds
     const int i = 1 + u * RF_THREADS + (int)threadIdx.x;
     const int64_t p = t0 - 1 + i;
     const uint64_t hk = s_k[i] >> sh;
-    const bool start = p + 1 < n && (s_k[i + 1] >> sh) == hk && !(p > 0 && (s_k[i - 1] >> sh) == hk);
+    const bool first = p < n && !(p > 0 && (s_k[i - 1] >> sh) == hk);
+    const bool start = first && p + 1 < n && (s_k[i + 1] >> sh) == hk;
+    if (PACKED && first && !start) s_chg[i] = 1;  // a run of one
     const uint64_t b = ballot(start);
     if (b == 0) continue;
     int at = 0;
@@ -886,20 +969,27 @@ __device__ __forceinline__ void refine_body(const RefineJobs& jobs, DevState* ds
         lo = min(lo, y + 1 - i);
       }
     }
-    for (int j = lo; j < len; ++j) s_chg[i + j] = 1;
+    for (int j = PACKED ? 0 : lo; j < len; ++j) s_chg[i + j] = 1;
   }
   __syncthreads();
+  uint64_t* kout = jb.k[res];
+  uint32_t* vout = jb.v[res];
 #pragma unroll
   for (int u = 0; u < RF_LD; ++u) {
     const int i = u * RF_THREADS + (int)threadIdx.x;
     if (i < RF_SPAN && s_chg[i]) {
-      keys[t0 - 1 + i] = s_k[i];
-      vals[t0 - 1 + i] = s_v[i];
+      kout[t0 - 1 + i] = s_k[i];
+      vout[t0 - 1 + i] = s_v[i];
     }
   }
   const int nlong = min(s_nlong, RF_TILE / (RF_SHORT + 1) + 1);
   for (int q = 0; q < nlong; ++q)
-    refine_long_run(jb, jobs.te, keys, vals, jb.k[par ^ 1], jb.v[par ^ 1], s_long[q], n, &s_len);
+    refine_long_run<PACKED>(jobs, jb, keys, vals, jb.k[par ^ 1], jb.v[par ^ 1], s_long[q], n, &s_len);
+}
+
+// Lowest bit of digit 1 in what the passes move.
+static inline int digit_base(const Ctx& c, const SortBufs& s) {
+  return c.packed ? s.sh1 - s.pk.drop + s.pk.key_shift() : s.sh1;
 }
 
 // Jobs of the histogram launch: a slice of `grid` workgroups per sort with
@@ -913,7 +1003,8 @@ static inline HistJobs hist_jobs(const Ctx& c, SortBufs* const* s, const int32_t
   int64_t n_max = 1;
   for (int i = 0; i < k; ++i) {
     if (s[i]->nd == 0) continue;
-    jobs.j[m++] = HistJob{s[i]->k[0], count[i], s[i]->status0, s[i]->nd, s[i]->id, s[i]->first, s[i]->sh1};
+    jobs.j[m++] = HistJob{s[i]->k[0], count[i], s[i]->status0, s[i]->nd, s[i]->id, s[i]->first,
+                           digit_base(c, *s[i])};
     n_max = std::max<int64_t>(n_max, s[i]->n_max);
     nd = std::max(nd, s[i]->nd);
   }
@@ -934,14 +1025,16 @@ static inline HistJobs hist_jobs(const Ctx& c, SortBufs* const* s, const int32_t
 // first + p (its lowest digit is left to the refine pass when first is 1).
 // The grid covers every sort's largest input; jobs.m is 0 when no sort has
 // that digit.
-static inline SortJobs sort_jobs(SortBufs* const* s, const int32_t* const* count, int k, int p, int64_t* grid) {
+static inline SortJobs sort_jobs(const Ctx& c, SortBufs* const* s, const int32_t* const* count, int k, int p,
+                                 int64_t* grid) {
   SortJobs jobs{};
   *grid = 0;
   for (int i = 0; i < k; ++i) {
     const int d = s[i]->first + p;
     if (d >= s[i]->nd) continue;
     jobs.j[jobs.m++] = SortJob{{s[i]->k[0], s[i]->k[1]}, {s[i]->v[0], s[i]->v[1]}, count[i], s[i]->status0,
-                               s[i]->status1, s[i]->tiles_max, s[i]->nd, s[i]->id, s[i]->first, s[i]->sh1, d};
+                               s[i]->status1, s[i]->tiles_max, s[i]->nd, s[i]->id, s[i]->first,
+                               digit_base(c, *s[i]), d};
     *grid += s[i]->tiles_max;
   }
   for (int i = jobs.m; i < N_SORTS; ++i) jobs.j[i] = jobs.j[0];
@@ -964,11 +1057,19 @@ static inline RefineJobs refine_jobs(Ctx& c, int64_t* grid, int* m_out) {
     if ((s == &c.sD || s == &c.sO) && !c.waits) continue;
     if (s == &c.sE && !c.crit) continue;
     if (!con && s->first == 0) continue;
+    const bool ends = s == &c.sE;
+    const int lane_bits = s == &c.sK ? c.sb : con ? c.tb : s == &c.sO ? c.nob : 0;
+    const int pid_shift = lane_bits + (con ? c.wb + 1 : ends ? c.wb1 : c.wb);
     jobs.j[m++] = RefineJob{{s->k[0], s->k[1]}, {s->v[0], s->v[1]}, counts[s->id], s->id, con ? 1 : 0,
-                            s->id, s->first ? s->sh1 : 0};
+                            s->id, s->first ? s->sh1 : 0, s->first ? digit_base(c, *s) : 0, s->pk, pid_shift,
+                            ends ? 1 : 0};
     n_max = std::max<int64_t>(n_max, s->n_max);
   }
+  jobs.ts = c.ev.ts;
   jobs.te = c.ev.te;
+  jobs.off = c.p.clock_offset;
+  jobs.W0 = c.W0;
+  jobs.W1 = c.W1;
   *grid = cdiv(n_max, RF_TILE);
   *m_out = m;
   return jobs;

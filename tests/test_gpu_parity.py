@@ -390,6 +390,30 @@ def test_small_window_sorts(H, rows, times):
     check(H, cols, tr.params, f"{rows} rows, {times}")
 
 
+@pytest.mark.parametrize("rows,times", [(140_000, "spread"), (140_000, "grid"), (1 << 18, "cluster"),
+                                        (460_000, "cluster")])
+@pytest.mark.parametrize("P,S,T", [(8, 16, 4), (8, 16, 8), (300, 16, 16), (1000, 64, 16)])
+def test_packed_sort_words(H, P, S, T, rows, times):
+    """Windows of 2^40 ns whose sort keys and rows do not fit one 64-bit word:
+    one bit of the timeline key left out, bits of the containment key too (its
+    launch bit stays), several of each, and too many (keys and rows apart).
+    Start times spread; on a coarse grid (long runs of equal keys); in a
+    cluster (long runs that differ in the bits left out)."""
+    tr = synth.random_small(9900 + P + T, n_rows=rows, window=1 << 40, n_procs=P, n_streams=S, n_threads=T,
+                            corr_range=rows // 2, flags=23)
+    cols = tr.columns()
+    dur = cols["te"] - cols["ts"]
+    w0 = tr.params["window_begin"]
+    if times == "grid":
+        step = (1 << 40) // 13
+        cols["ts"] = w0 + (cols["ts"] - w0) // step * step
+    elif times == "cluster":
+        near = np.random.default_rng(rows).random(rows) < 0.995
+        cols["ts"] = np.where(near, w0 + 1000 + (cols["ts"] - w0) % 900, cols["ts"])
+    cols["te"] = cols["ts"] + dur % 5_000_000
+    check(H, cols, tr.params, f"{P} processes, {S} streams, {T} threads, {rows} rows, {times}")
+
+
 THREE_STREAMS = {
     "long runs": lambda H: test_long_runs_of_equal_op_starts(H),
     "short runs across tiles": lambda H: test_wide_keys_short_runs_across_tiles(H),
