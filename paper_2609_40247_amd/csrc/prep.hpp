@@ -21,7 +21,7 @@ namespace hx {
 constexpr int PREP_THREADS = 512;
 // Rows per thread: 8 in general; 2 for small windows, whose few tiles of 4096
 // rows would leave most of the chip idle while each took its four batches of
-// loads one after another (one tile of 1500 rows: 9.7 against 5.9 us).
+// loads one after another (1500 rows: 9.7 against 7.8 us).
 constexpr int PREP_ITEMS = 8, PREP_ITEMS_SMALL = 2;
 
 struct PrepArgs {

@@ -177,7 +177,8 @@ __device__ __forceinline__ void tile_sort_body(const TileSortJobs& jobs, DevStat
   const int rb = bits_of(ext[1] - bits.seg0) + bits.tb;
   // Two passes order the tile by the top 16 of these bits: of 4096 keys few
   // share them, and those that do count their way past one
-  // another.  (Sorting every digit took five passes of about 3 us.)
+  // another.  (With every digit sorted the launch took 25 us on 60k rows,
+  // against 21.)
   int sh = rb > 16 ? rb - 16 : 0;
   if (rb > 0) tile_pass(lds, ds, key, val, bits, sh, tn);
   if (rb > 8) tile_pass(lds, ds, key, val, bits, sh + 8, tn);
