@@ -552,15 +552,25 @@ static int enqueue_locked(Ctx& c, DeviceStreams* dsx) {
   return hipGetLastError() == hipSuccess ? HERSCHEL_OK : HERSCHEL_EDEVICE;
 }
 
-static DeviceStreams* enqueue_setup() {
-  static bool lds_attr = false;
-  if (!lds_attr) {
-    names_set_lds_attr();
-    level_set_lds_attr();
-    lds_attr = true;
+// The kernels whose launches take more than the default 64 KB of dynamic LDS
+// (a small window's tile sort takes 65 KB) get their limit raised once per
+// device; false if the current device refuses it (the caller holds
+// g_enqueue_mutex).
+static bool raise_lds_limits() {
+  static bool done[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+  if (!done[dev]) {
+    if (names_set_lds_attr() != hipSuccess || level_set_lds_attr() != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    done[dev] = true;
   }
-  return device_streams();
+  return true;
 }
+
+static DeviceStreams* enqueue_setup() { return raise_lds_limits() ? device_streams() : nullptr; }
 
 static int enqueue(Ctx& c) {
   std::lock_guard<std::mutex> lock(g_enqueue_mutex);
@@ -947,13 +957,7 @@ int herschel_trace_analyze_static(const herschel_events* ev, int64_t n, const he
     if (!base) return HERSCHEL_EDEVICE;
     layout_workspace(c, (char*)base);
     redirect_outputs(c);
-    static bool lds_attr = false;
-    if (!lds_attr) {
-      names_set_lds_attr();
-      level_set_lds_attr();
-      lds_attr = true;
-    }
-    code = enqueue_locked(c, nullptr);
+    code = raise_lds_limits() ? enqueue_locked(c, nullptr) : HERSCHEL_EDEVICE;
   }
   if (code) return code;
   herschel_counters h;

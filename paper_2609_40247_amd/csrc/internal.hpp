@@ -211,10 +211,10 @@ bool sol_uses_tables(int NOP);
 
 int64_t prep_tile_rows(bool small);
 int64_t union_tile_elems(bool small);
-void names_set_lds_attr();
+hipError_t names_set_lds_attr();
 // small windows: the call up to the critical path's walk, fused level by level
 void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks, int passes);
-void level_set_lds_attr();
+hipError_t level_set_lds_attr();
 
 // digit histograms: keys per workgroup (at least), most workgroups per sort
 constexpr int HIST_CHUNK = 4096;

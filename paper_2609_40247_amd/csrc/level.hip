@@ -429,8 +429,8 @@ void launch_levels(Ctx& c, SortBufs* const* ss, const int32_t* const* cc, int ks
   l.launch();
 }
 
-void level_set_lds_attr() {
-  (void)hipFuncSetAttribute((const void*)k_level, hipFuncAttributeMaxDynamicSharedMemorySize, NM_LDS_NAMES * 32);
+hipError_t level_set_lds_attr() {
+  return hipFuncSetAttribute((const void*)k_level, hipFuncAttributeMaxDynamicSharedMemorySize, NM_LDS_NAMES * 32);
 }
 
 }  // namespace hx

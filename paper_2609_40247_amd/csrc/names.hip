@@ -74,9 +74,9 @@ void launch_opnames(Ctx& c) {
 
 int names_lds_limit() { return NM_LDS_NAMES; }
 
-void names_set_lds_attr() {
-  (void)hipFuncSetAttribute((const void*)k_names_partial, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            NM_LDS_NAMES * 32);
+hipError_t names_set_lds_attr() {
+  return hipFuncSetAttribute((const void*)k_names_partial, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             NM_LDS_NAMES * 32);
 }
 
 }  // namespace hx

@@ -1,0 +1,119 @@
+"""What the library asks of the HIP runtime, on a machine without a GPU.
+
+The built library runs in a child process over a stand-in for the runtime
+(``fake_hip.c``) that logs every launch, event and attribute call and runs no
+kernel: the host side of a call (which kernels, on which streams, in which
+order, with what set before) without its device side."""
+from __future__ import annotations
+
+import json
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+# The child must not load torch (its HIP runtime would bind first): the
+# marshalling module gets an empty stand-in for it.
+PRELUDE = textwrap.dedent(r"""
+    import ctypes, json, sys, types
+    sys.path.insert(0, @ROOT@)
+    sys.modules["torch"] = types.ModuleType("torch")
+    fake = ctypes.CDLL(@FAKE@, mode=ctypes.RTLD_GLOBAL)
+    fake.fake_log.restype = ctypes.c_char_p
+    from paper_2609_40247_amd import herschel as H
+    lib = H.load("release")
+
+    def params(n=0, **kw):
+        q = dict(window_begin=0, window_end=30 * 10**9, gap_threshold=0, n_procs=1, n_streams=4, n_threads=1,
+                 n_names=2000, n_op_names=100, flags=3, workspace=1 << 40, workspace_bytes=1 << 50)
+        q.update(kw)
+        return H.HerschelParams(**q)
+
+    EV = H.HerschelEvents(**{k: (1 << 44) + 256 * i for i, (k, _) in enumerate(H.HerschelEvents._fields_)})
+
+    def outputs(*without):
+        o = {k: (1 << 45) + 4096 * i for i, (k, _) in enumerate(H.HerschelOutputs._fields_)
+             if k != "gap_capacity" and k not in without}
+        return H.HerschelOutputs(gap_capacity=1 << 20, **o)
+
+    def log():
+        t = fake.fake_log().decode().splitlines()
+        fake.fake_clear()
+        return t
+
+    def device(d=0, word=0, attr_result=0):
+        fake.fake_set(d, word, attr_result)
+
+    out = []
+""")
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    from paper_2609_40247_amd import build, herschel
+    if not os.path.exists(herschel.library_path("release")):
+        build.build(checked=False)
+    so = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "fake_hip.c")], check=True)
+    return so
+
+
+def child(fake, body, **env):
+    """Runs `body` over the stand-in; what it appends to `out`."""
+    src = (PRELUDE + textwrap.dedent(body) + "\nprint(json.dumps(out))\n").replace("@ROOT@", repr(ROOT)).replace(
+        "@FAKE@", repr(fake))
+    r = subprocess.run([sys.executable, "-c", src], capture_output=True, text=True, timeout=120,
+                       env={**os.environ, **env})
+    assert r.returncode == 0, r.stderr[-2000:]
+    return json.loads(r.stdout.splitlines()[-1])
+
+
+def launches(log):
+    return [line.split()[1] for line in log if line.startswith("launch ")]
+
+
+def test_calls_are_seen(fake):
+    """The stand-in serves the library: a small window's launches, in order."""
+    (code, log), = child(fake, """
+        device()
+        o = outputs()
+        out.append((H.herschel_trace_analyze(EV, 1500, params(), o), log()))
+    """)
+    k = launches(log)
+    assert code == 0 and len(k) == 9 and "k_finalize" in k[-1] and all("k_level" in x for x in k[:-1]), (code, k)
+
+
+@pytest.mark.parametrize("entry", ["analyze", "static"])
+def test_lds_limit_is_raised_on_every_device(fake, entry):
+    """Launches with more dynamic LDS than the default 64 KB: the kernel's limit
+    was raised on that device before, and a device that refuses it fails the
+    call instead of the launch."""
+    res = child(fake, f"""
+        call = H.herschel_trace_analyze{"_static" if entry == "static" else ""}
+        for d in (0, 1, 0, 3):
+            device(d)
+            out.append((d, call(EV, 1500, params(), outputs()), log()))
+        device(5, 0, 1)
+        out.append((5, call(EV, 1500, params(), outputs()), log()))
+        device(5)
+        out.append((5, call(EV, 1500, params(), outputs()), log()))
+    """)
+    raised = set()
+    for d, code, log in res[:4] + res[5:]:
+        assert code == 0
+        big = 0
+        for line in log:
+            w = line.split()
+            if w[0] == "attribute":
+                raised.add((w[1], int(w[-1]), int(w[3])))
+            elif w[0] == "launch" and int(w[7]) > 65536:
+                big += 1
+                assert any(f == w[1] and v == d and size >= int(w[7]) for f, v, size in raised), line
+        assert big
+    d, code, log = res[4]
+    assert code == -5 and not launches(log)
