@@ -68,6 +68,7 @@ struct Ctx {
   int64_t W0 = 0, W1 = 0, W = 0, thr = 0;
   int P = 0, S = 0, T = 0, NN = 0, NOP = 0;
   bool small = false;  // launched level by level
+  bool captured = false;  // into a graph that later calls replay
   bool packed = false;  // the sorts move packed words (PackFmt)
   bool contain = false, overlap = false, waits = false, sol = false, crit = false, graph = false;
   int NG = 0;                          // graph nodes (graph replay separation)
