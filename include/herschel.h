@@ -289,8 +289,9 @@ int herschel_workspace_size(int64_t n, const herschel_params *p, size_t *bytes);
  * params->flags, a call whose event columns, n, parameters (all but
  * hip_stream) and output pointers equal those of one of the last four such
  * argument sets captured on the device replays that call's captured HIP
- * graph (the buffers' contents may differ); without it every call launches
- * its kernels directly.  Calls overlapping from several host threads are
+ * graph (the buffers' contents may differ); without it, and with
+ * HERSCHEL_OUT_WAITS above 450,000 rows, every call launches its kernels
+ * directly.  Calls overlapping from several host threads are
  * serialised while they enqueue. */
 int herschel_trace_analyze(const herschel_events *ev, int64_t n, const herschel_params *p,
                            herschel_outputs *out);

@@ -139,3 +139,15 @@ def test_captured_op_name_tables_wait_for_the_sorted_lists(fake):
     stream = log[tables].split()[9]
     assert f"wait {lists} stream {stream}" in log[refine:tables], log
     assert code == 0 and sum(line.startswith("graph ") for line in log) == 1
+
+
+@pytest.mark.parametrize("rows,captured", [(400_000, True), (600_000, False)])
+def test_idle_coincidence_is_captured_on_one_stream_only(fake, rows, captured):
+    """With the idle coincidence a window that takes three streams is launched
+    directly also when replay is asked for."""
+    (code, log), = child(fake, f"""
+        device()
+        out.append((H.herschel_trace_analyze(EV, {rows}, params(flags=7 | H.REPLAY), outputs()), log()))
+    """)
+    assert code == 0 and launches(log)
+    assert any(line.startswith("capture ") for line in log) == captured
