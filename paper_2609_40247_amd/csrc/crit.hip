@@ -136,7 +136,12 @@ void launch_crit_walk(Ctx& c) {
   CritArgs a = crit_args(c);
   hipLaunchKernelGGL(k_crit_walk, dim3((unsigned)cdiv(c.P, 256)), dim3(256), 0, c.st, a);
   if (!c.crit_deferred) {
-    launch_crit_strides(c, a);
+    // (a larger window's strides are six launches more, 13 us that nearly every
+    // window of a batch would pay for nothing: straight to the doubling)
+    if (c.small)
+      launch_crit_strides(c, a);
+    else
+      a.when = CP_MORE_STRIDES;
     launch_crit_rounds(c, a);
     launch_crit_marks(c, a, 0);
     return;

@@ -101,6 +101,7 @@ struct CritArgs {
   int hop_max;   // strides of a process's path before the doubling takes over
   int32_t* sq;   // [2n] squared pointers, with ptr0 in turn (the kernel ends' buffer)
   uint32_t left; // the charging pass waits while one of these bits of crit_more is set
+  uint32_t when; // the doubling runs if one of these is
 };
 
 // DevState::crit_more: a walk stopped short, and so did the strides.
@@ -601,7 +602,7 @@ __device__ __forceinline__ void crit_mark_local_body(const CritArgs& a, CritMark
 // nothing does nothing: the path's entries are marked.
 __device__ __forceinline__ void crit_round_body(const CritArgs& a, uint32_t bx, uint32_t gx) {
   const int rd = a.round;
-  if (!(a.ds->crit_more & CP_MORE_DOUBLING)) return;
+  if (!(a.ds->crit_more & a.when)) return;
   if (rd > 0 && a.ds->crit_new[rd - 1] == 0) return;
   const int32_t* in = rd == 0 ? a.ptr1 : (rd & 1) ? a.ptr0 : a.ptr1;
   int32_t* out = (rd & 1) ? a.ptr1 : a.ptr0;
@@ -721,6 +722,7 @@ static inline CritArgs crit_args(const Ctx& c) {
   a.round = 0;
   a.walk_max = c.crit_walk_max;
   a.left = CP_MORE_STRIDES | CP_MORE_DOUBLING;
+  a.when = CP_MORE_DOUBLING;
   // the kernel ends' buffer is free once the host records' pass is done
   a.sq = reinterpret_cast<int32_t*>(c.sE.k[0]);
   // (a lower walk limit, for tests, limits the strides as well)

@@ -26,7 +26,7 @@ PRELUDE = textwrap.dedent(r"""
     fake = ctypes.CDLL(@FAKE@, mode=ctypes.RTLD_GLOBAL)
     fake.fake_log.restype = ctypes.c_char_p
     from paper_2609_40247_amd import herschel as H
-    lib = H.load("release")
+    lib = H.load()
 
     def params(n=0, **kw):
         q = dict(window_begin=0, window_end=30 * 10**9, gap_threshold=0, n_procs=1, n_streams=4, n_threads=1,
@@ -151,3 +151,21 @@ def test_idle_coincidence_is_captured_on_one_stream_only(fake, rows, captured):
     """)
     assert code == 0 and launches(log)
     assert any(line.startswith("capture ") for line in log) == captured
+
+
+@pytest.mark.parametrize("rows", [400_000, 600_000, 20_000_000])
+def test_inline_critical_path_launches(fake, rows):
+    """A batch marks each window's critical path in line, with what a long path
+    needs beyond the walk: launches with nothing to do in nearly every window.
+    They are no more than the rounds of doubling over the window's events (two
+    more for a small window, whose strides are two launches)."""
+    (code, log), = child(fake, f"""
+        import numpy as np
+        device()
+        offs = np.array([0, {rows}, {2 * rows}])
+        out.append((H.herschel_trace_analyze_batch(EV, offs, [params(flags=19)] * 2, [outputs()] * 2), log()))
+    """)
+    needed = ("elist", "kernels", "host", "last", "ops", "rows", "local", "walk", "mark_local", "attr")
+    rest = [k for k in launches(log) if "k_crit_" in k and not any(f"k_crit_{x}E" in k for x in needed)]
+    rounds = (2 * rows - 1).bit_length() + 1
+    assert code == 0 and len(rest) <= 2 * (rounds + (2 if rows <= 450_000 else 0)), rest[:40]
