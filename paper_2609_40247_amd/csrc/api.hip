@@ -768,7 +768,7 @@ static int wait_mailbox(hipStream_t st, Mailbox* mb, int64_t seq, herschel_count
 
 // The rest of the critical path's marking when the call left it out and a
 // walk stopped short (DevState::crit_more), on the caller's stream, waited
-// for: the strides, and the doubling if those stop short as well.
+// for: the strides, and the further levels if those stop short as well.
 static int finish_crit(Ctx& c, uint32_t more) {
   if (!c.crit_deferred || !more) return HERSCHEL_OK;
   if (!c.small) {
@@ -923,7 +923,7 @@ int herschel_trace_analyze(const herschel_events* ev, int64_t n, const herschel_
     c.mailbox = thread_mailbox();
     c.mailbox_seq = c.mailbox ? ++tl_mailbox_seq : 0;
   }
-  // the critical path's doubling pass is needed only when a walk stopped
+  // what marks long critical paths is needed only when a walk stopped
   // short: it is enqueued after the call if the call reports so (a replayed
   // graph keeps it inline)
   c.crit_deferred = c.crit && !(c.p.flags & HERSCHEL_REPLAY);
@@ -958,7 +958,7 @@ int herschel_trace_analyze_static(const herschel_events* ev, int64_t n, const he
   int code = check_and_plan(c, ev, n, p, out);
   if (code) return code;
   if (layout_workspace(c, nullptr) > (size_t)HERSCHEL_STATIC_SCRATCH_BYTES) return HERSCHEL_ETOOBIG;
-  c.crit_deferred = c.crit;  // the critical path's doubling pass only if the call reports it needed
+  c.crit_deferred = c.crit;  // what marks long critical paths only if the call reports it needed
   {
     std::lock_guard<std::mutex> lock(g_enqueue_mutex);
     void* base = static_scratch();

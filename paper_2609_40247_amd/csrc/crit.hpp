@@ -33,12 +33,13 @@
 // marks each one (the entries of the path into tiles); a workgroup per tile
 // that holds a marked entry marks its chain inside the tile.  A path with
 // more than walk_max exits (rows in no order put an exit at nearly every
-// step) is walked again in strides of CP_STRIDE exits, over pointers squared
-// CP_SQUARES times, and a thread per stride marks the exits inside it; one
-// with more than hop_max strides is marked by pointer doubling over the exits
-// from the marked ones (round r marks the exits 2^r steps behind while the
-// pointers double, until a round adds nothing).  Then the tiles are marked
-// again.  A last pass charges the marked steps.
+// step) is walked again in strides of CP_STRIDE exits, over pointers that
+// follow that many, and a thread per stride marks the exits inside it; one
+// with more than hop_max strides is walked over pointers of further levels
+// (CP_STRIDE steps of the level below each), and level by level, from the
+// highest down, the events marked so far mark the steps that the level below
+// takes from them.  Then the tiles are marked again.  A last pass charges the
+// marked steps.
 #pragma once
 
 #include "internal.hpp"
@@ -58,6 +59,15 @@ enum : uint8_t {
 };
 constexpr int CP_PARTS = 8;         // per process: length, then the seven parts
 constexpr int CP_LDS_PROCS = 64;    // processes whose parts a workgroup sums in LDS
+
+// DevState::crit_more: a walk stopped short, and so did the strides.
+enum : uint32_t { CP_MORE_STRIDES = 1, CP_MORE_FAR = 2 };
+constexpr int CP_STRIDE_LOG = 5;
+constexpr int CP_STRIDE = 1 << CP_STRIDE_LOG;
+constexpr int CP_HOPS = 512;
+// Levels of pointers.  Over the highest in use a path is at most CP_HOPS hops
+// long (over three levels up to 2^24 events; beyond, one thread takes more).
+constexpr int CP_LEVELS = 3;
 
 struct CritArgs {
   int64_t n;
@@ -87,8 +97,7 @@ struct CritArgs {
   int32_t* pred;  // [2n] release of each event (-1 none)
   uint8_t* code;  // [2n] its part and whom it is charged to
   uint8_t* mark;  // [2n] on the path (zeroed with the state)
-  int32_t* ptr0;  // [2n] doubling pointers, ping-pong
-  int32_t* ptr1;
+  int32_t* lv[CP_LEVELS + 1];  // [2n] each: every event's exit, then 32 steps of the level below
   uint32_t* lastc1;  // [n] by containment position: last child's position + 1 (zeroed)
   uint8_t* hasnext;  // [n] by containment position: a later sibling exists (zeroed)
   uint64_t* zmax;    // [P] largest end - W0 + 1 (zeroed)
@@ -96,19 +105,16 @@ struct CritArgs {
   int64_t* crit_time;
   uint8_t* crit_flags;
   int64_t* crit_proc;
-  int round;
   int walk_max;  // exits a process's walk marks before the strides take over
-  int hop_max;   // strides of a process's path before the doubling takes over
-  int32_t* sq;   // [2n] squared pointers, with ptr0 in turn (the kernel ends' buffer)
+  int hop_max;   // strides of a process's path before the further levels do
+  int levels;    // the highest of these
+  const int32_t* jump_in;  // the jump's pointers, its steps, its result
+  int32_t* jump_out;
+  int jump_steps;
+  int fill;      // the level of a filling pass
+  uint32_t need; // the passes for long paths run if one of these bits of crit_more is set
   uint32_t left; // the charging pass waits while one of these bits of crit_more is set
-  uint32_t when; // the doubling runs if one of these is
 };
-
-// DevState::crit_more: a walk stopped short, and so did the strides.
-enum : uint32_t { CP_MORE_STRIDES = 1, CP_MORE_DOUBLING = 2 };
-constexpr int CP_SQUARES = 5;
-constexpr int CP_STRIDE = 1 << CP_SQUARES;
-constexpr int CP_HOPS = 512;
 
 // Tiles of event ids for the two-level marking: CP_TE ids per workgroup of
 // CP_LT threads, in LDS.
@@ -412,7 +418,7 @@ __device__ __forceinline__ void crit_rows_body(const CritArgs& a, uint32_t bx, u
   }
 }
 
-// Each event's exit from its tile (into ptr1): the release of the last
+// Each event's exit from its tile (into lv[0]): the release of the last
 // event of its release chain inside the tile (-1 where the chain ends in the
 // tile).  In LDS every event points to its release inside the tile, or to
 // itself when the release lies outside it or there is none; pointer jumping
@@ -453,7 +459,7 @@ __device__ __forceinline__ void crit_local_body(const CritArgs& a, CritLocalLds&
 #pragma unroll
   for (int k = 0; k < CP_EPT; ++k) {
     const int i = tid + k * CP_LT;
-    if (i < tn) a.ptr1[tb + i] = a.pred[tb + s_j[i]];
+    if (i < tn) a.lv[0][tb + i] = a.pred[tb + s_j[i]];
   }
 }
 
@@ -474,31 +480,18 @@ __device__ __forceinline__ void crit_walk_body(const CritArgs& a, uint32_t bx) {
       atomicOr(&a.ds->crit_more, (uint32_t)CP_MORE_STRIDES);
       break;
     }
-    e = a.ptr1[e];
+    e = a.lv[0][e];
   }
 }
 
-// One squaring of the exit pointers: out[e] = in[in[e]].
-__device__ __forceinline__ void crit_square_body(const CritArgs& a, uint32_t bx, uint32_t gx) {
-  if (!a.ds->crit_more) return;
-  const int32_t* in = a.round == 0 ? a.ptr1 : (a.round & 1) ? a.ptr0 : a.sq;
-  int32_t* out = (a.round & 1) ? a.sq : a.ptr0;
-  const int64_t ne = 2 * a.n;
-  for (int64_t i = (int64_t)bx * 256 + threadIdx.x; i < ne; i += (int64_t)gx * 256) {
-    const int32_t t = in[i];
-    out[i] = t >= 0 && in_range(a.ds, t, ne) ? in[t] : -1;
-  }
-}
-static_assert(CP_SQUARES % 2 == 1, "the last squaring writes ptr0");
-
-// The same pointers by following the exits CP_STRIDE times.
+// Pointers over jump_steps steps of other pointers.
 __device__ __forceinline__ void crit_jump_body(const CritArgs& a, uint32_t bx, uint32_t gx) {
-  if (!a.ds->crit_more) return;
+  if (!(a.ds->crit_more & a.need)) return;
   const int64_t ne = 2 * a.n;
   for (int64_t i = (int64_t)bx * 256 + threadIdx.x; i < ne; i += (int64_t)gx * 256) {
     int64_t e = i;
-    for (int k = 0; k < CP_STRIDE && e >= 0 && in_range(a.ds, e, ne); ++k) e = a.ptr1[e];
-    a.ptr0[i] = (int32_t)e;
+    for (int k = 0; k < a.jump_steps && e >= 0 && in_range(a.ds, e, ne); ++k) e = a.jump_in[e];
+    a.jump_out[i] = (int32_t)e;
   }
 }
 
@@ -512,7 +505,7 @@ struct CritStridesLds {
 __device__ __forceinline__ void crit_strides_body(const CritArgs& a, CritStridesLds& lds, uint32_t bx, uint32_t gx) {
   auto& s_hop = lds.s_hop;
   auto& s_n = lds.s_n;
-  if (!a.ds->crit_more) return;
+  if (!(a.ds->crit_more & a.need)) return;
   const int64_t ne = 2 * a.n;
   for (int p = bx; p < a.P; p += gx) {
     __syncthreads();  // the last process's reads
@@ -522,17 +515,51 @@ __device__ __forceinline__ void crit_strides_body(const CritArgs& a, CritStrides
       int s = 0;
       for (; s < a.hop_max && e >= 0 && in_range(a.ds, e, ne); ++s) {
         s_hop[s] = (int32_t)e;
-        e = a.ptr0[e];
+        e = a.lv[1][e];
       }
       s_n = s;
-      if (e >= 0) atomicOr(&a.ds->crit_more, (uint32_t)CP_MORE_DOUBLING);
+      if (e >= 0) atomicOr(&a.ds->crit_more, (uint32_t)CP_MORE_FAR);
     }
     __syncthreads();
     if ((int)threadIdx.x >= s_n) continue;
     int64_t e = s_hop[threadIdx.x];
     for (int k = 0; k < CP_STRIDE && e >= 0 && in_range(a.ds, e, ne); ++k) {
       a.mark[e] = 1;
-      e = a.ptr1[e];
+      e = a.lv[0][e];
+    }
+  }
+}
+
+// Each process's path over the pointers of the highest level: an event of it
+// is marked with that level plus one.  (While the levels are filled in, a mark
+// is one more than the highest level that steps on the event.)
+__device__ __forceinline__ void crit_far_walk_body(const CritArgs& a, uint32_t bx) {
+  if (!(a.ds->crit_more & a.need)) return;
+  const int p = bx * 256 + threadIdx.x;
+  if (p >= a.P) return;
+  const uint32_t z = a.zrow1[p];
+  const int64_t ne = 2 * a.n;
+  const int32_t* top = a.lv[a.levels];
+  int64_t e = z ? 2 * (int64_t)(z - 1) + 1 : -1;
+  // (a path holds an event once: no more hops than this)
+  for (int64_t s = ne >> (CP_STRIDE_LOG * a.levels); s >= 0 && e >= 0 && in_range(a.ds, e, ne); --s) {
+    a.mark[e] = (uint8_t)(a.levels + 1);
+    e = top[e];
+  }
+}
+
+// From every event that level `fill` or a higher one steps on, the steps of
+// the level below up to the next such event.
+__device__ __forceinline__ void crit_far_fill_body(const CritArgs& a, uint32_t bx, uint32_t gx) {
+  if (!(a.ds->crit_more & a.need)) return;
+  const int64_t ne = 2 * a.n;
+  const int32_t* step = a.lv[a.fill - 1];
+  for (int64_t i = (int64_t)bx * 256 + threadIdx.x; i < ne; i += (int64_t)gx * 256) {
+    if ((int)a.mark[i] <= a.fill) continue;
+    int64_t e = step[i];
+    for (int k = 1; k < CP_STRIDE && e >= 0 && in_range(a.ds, e, ne); ++k) {
+      a.mark[e] = (uint8_t)a.fill;
+      e = step[e];
     }
   }
 }
@@ -593,37 +620,6 @@ __device__ __forceinline__ void crit_mark_local_body(const CritArgs& a, CritMark
   for (int k = 0; k < CP_MEPT; ++k) {
     const int i = tid + k * CP_MLT;
     if (i < tn && s_m[i]) a.mark[tb + i] = 1;
-  }
-}
-
-// One doubling round over the exits (only when the strides stopped short): every
-// marked event marks the event its pointer names (2^round exits back), and
-// every pointer is replaced by its target's.  A round after one that marked
-// nothing does nothing: the path's entries are marked.
-__device__ __forceinline__ void crit_round_body(const CritArgs& a, uint32_t bx, uint32_t gx) {
-  const int rd = a.round;
-  if (!(a.ds->crit_more & a.when)) return;
-  if (rd > 0 && a.ds->crit_new[rd - 1] == 0) return;
-  const int32_t* in = rd == 0 ? a.ptr1 : (rd & 1) ? a.ptr0 : a.ptr1;
-  int32_t* out = (rd & 1) ? a.ptr1 : a.ptr0;
-  const int64_t ne = 2 * a.n;
-  for (int64_t i0 = (int64_t)bx * 256; i0 < ne; i0 += (int64_t)gx * 256) {  // uniform per workgroup
-    const int64_t i = i0 + threadIdx.x;
-    bool added = false;
-    if (i < ne) {
-      const int32_t t = in[i];
-      if (t >= 0 && in_range(a.ds, t, ne)) {
-        if (a.mark[i] && !a.mark[t]) {
-          a.mark[t] = 1;
-          added = true;
-        }
-        out[i] = in[t];
-      } else {
-        out[i] = -1;
-      }
-    }
-    const uint64_t b = ballot(added);
-    if (b && lane_id() == 0) atomicAdd(&a.ds->crit_new[rd], (uint32_t)popc(b));
   }
 }
 
@@ -710,8 +706,13 @@ static inline CritArgs crit_args(const Ctx& c) {
   a.pred = c.crit_pred;
   a.code = c.crit_code;
   a.mark = c.crit_mark;
-  a.ptr0 = c.crit_ptr[0];
-  a.ptr1 = c.crit_ptr[1];
+  a.lv[0] = c.crit_ptr[0];
+  a.lv[1] = c.crit_ptr[1];
+  // the kernel ends' buffers are free once the host records' pass is done
+  a.lv[2] = reinterpret_cast<int32_t*>(c.sE.k[0]);
+  a.lv[3] = reinterpret_cast<int32_t*>(c.sE.k[1]);
+  static_assert(CP_LEVELS == 3, "a buffer for every level");
+  a.levels = ((int64_t)CP_HOPS << (2 * CP_STRIDE_LOG)) < 2 * c.n ? 3 : 2;
   a.lastc1 = c.crit_lastc1;
   a.hasnext = c.crit_hasnext;
   a.zmax = c.crit_zmax;
@@ -719,14 +720,11 @@ static inline CritArgs crit_args(const Ctx& c) {
   a.crit_time = c.o.crit_time;
   a.crit_flags = c.o.crit_flags;
   a.crit_proc = c.o.crit_proc;
-  a.round = 0;
   a.walk_max = c.crit_walk_max;
-  a.left = CP_MORE_STRIDES | CP_MORE_DOUBLING;
-  a.when = CP_MORE_DOUBLING;
-  // the kernel ends' buffer is free once the host records' pass is done
-  a.sq = reinterpret_cast<int32_t*>(c.sE.k[0]);
   // (a lower walk limit, for tests, limits the strides as well)
   a.hop_max = c.crit_walk_max < CP_WALK ? c.crit_walk_max : CP_HOPS;
+  a.left = CP_MORE_STRIDES | CP_MORE_FAR;
+  a.need = 0;
   return a;
 }
 

@@ -9,6 +9,8 @@ processes, the largest window), error paths, and determinism.
 """
 from __future__ import annotations
 
+import time
+
 import numpy as np
 import pytest
 
@@ -1313,6 +1315,86 @@ def test_crit_long_path(H, shape):
     cols, p = _queue_bound_trace(100_000, shuffle=shape == "shuffled")
     (code, g), _ = check(H, cols, p, f"long critical path, {shape}")
     assert (g["crit_flags"] == 3).sum() >= 99_000
+
+
+@pytest.mark.parametrize("entry", ["analyze", "static", "batch", "replay"])
+def test_crit_path_beyond_the_strides(H, entry):
+    """Paths of more exits than the strides follow (16,384), marked over further
+    levels of pointers: two levels in windows of 120,000 and 480,000 rows (each
+    side of the level-by-level limit), three in one of 600,000; after the call
+    or, in a batch and in replays, in line.  A batch mixes them with a window
+    whose walk suffices; replays find such a window and a long path in turn."""
+    sizes = {"static": (60_000,), "replay": (60_000, 240_000)}.get(entry, (60_000, 240_000, 300_000))
+    made = [_queue_bound_trace(k, True, seed=k) for k in sizes]
+    if entry == "batch":
+        made.insert(1, _queue_bound_trace(250_000, False))
+        made.append(_queue_bound_trace(2_000, True))
+    want = [oracle.analyze(c, p, gap_capacity=len(c["ts"]) + 1) for c, p in made]
+    for (c, p), (code, o) in zip(made, want):
+        assert code == 0 and (o["crit_flags"] == 3).sum() >= 0.9 * len(c["ts"]) / 2
+    if entry == "batch":
+        cols = {k: np.concatenate([c[k] for c, _ in made]) for k in made[0][0]}
+        offs = np.cumsum([0] + [len(c["ts"]) for c, _ in made]).astype(np.int64)
+        ans = [H.Analyzer(p, len(c["ts"]), gap_capacity=len(c["ts"]) + 1) for c, p in made]
+        for a in ans:
+            a.prefill()
+        big = max(ans, key=lambda a: a.ws_bytes)
+        p0 = ans[0]._params_struct(big.ws.data_ptr(), big.ws_bytes)
+        d = H.device_columns(cols)
+        code = H.herschel_trace_analyze_batch(H.events_struct(d), offs, [p0] + [a.params for a in ans[1:]],
+                                              [a.outs for a in ans])
+        torch.cuda.synchronize()
+        for (c, p), a, w in zip(made, ans, want):
+            assert_same((code, a.results(len(c["ts"]))), w, p, f"batch, {len(c['ts'])} rows")
+        return
+    for (c, p), w in zip(made, want):
+        n = len(c["ts"])
+        q = dict(p, flags=17 | H.REPLAY) if entry == "replay" else p
+        an = H.Analyzer(q, n, gap_capacity=n + 1, workspace=entry != "static")
+        ordered = _queue_bound_trace(n // 2, False)[0]
+        d = H.device_columns(c)
+        ev = H.events_struct(d)
+        for k in range(5 if entry == "replay" else 1):
+            cc, ww = c, w
+            if k % 2:
+                cc, ww = ordered, oracle.analyze(ordered, p, gap_capacity=n + 1)
+            for name, v in d.items():
+                v.copy_(torch.from_numpy(np.ascontiguousarray(cc[name])))
+            an.prefill()
+            torch.cuda.synchronize()
+            if entry == "static":
+                code = H.herschel_trace_analyze_static(ev, n, an.params, an.outs)
+            else:
+                code = an.run(ev, n)
+            torch.cuda.synchronize()
+            assert_same((code, an.results(n)), ww, p, f"{entry}, {n} rows, call {k}")
+
+
+def _best_ms(run, reps=8):
+    best = float("inf")
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        run()
+        best = min(best, time.perf_counter() - t0)
+    return best * 1e3
+
+
+def test_crit_long_path_time(H):
+    """A path of 440,000 events in rows of no order takes less than 3.5 times the
+    call in delivery order: the strides, when they do not reach, stand before
+    levels that do (2.3 times), not before as many rounds of doubling as without
+    them (4.7 times; with the doubling alone 2.9)."""
+    ms = []
+    for shuffle in (False, True):
+        cols, p = _queue_bound_trace(220_000, shuffle)
+        n = len(cols["ts"])
+        an = H.Analyzer(p, n, gap_capacity=n + 1)
+        d = H.device_columns(cols)
+        ev = H.events_struct(d)
+        assert an.run(ev, n) == 0
+        ms.append(_best_ms(lambda: an.run(ev, n)))
+    assert ms[1] < 3.5 * ms[0], ms
 
 
 @pytest.mark.parametrize("walk", ["0", "3"])
