@@ -5,7 +5,8 @@
 //
 //   tile sort: a workgroup sorts TS_TILE keys of a list in LDS (two passes of
 //              the radix passes' ranking over the top bits that
-//              tell the keys apart, then runs of equal bits by counting), and writes the
+//              tell the keys apart, then short runs of equal bits by counting;
+//              with a longer run, passes over every bit), and writes the
 //              tile and every TS_STEP-th key of it;
 //   merge:     a thread per key counts, in every other tile, the keys that
 //              come before it; with its place in its own tile the sum is its
@@ -62,21 +63,21 @@ struct TileBits {
   }
 };
 
-// One stable pass over the tile by 8 bits of bits(key) >> sh.  Item j of
+// One stable pass over the tile by the digits dg (one per item, below 256; of
+// positions from tn on 255, so that they stay last).  Item j of
 // lane l is the tile's position (wave * TS_ITEMS + j) * 64 + l: items in
-// order, lanes in order is the tile's order.  Positions from tn on stay last.
+// order, lanes in order is the tile's order.
 __device__ __forceinline__ void tile_pass(TileSortLds& lds, DevState* ds, uint64_t (&key)[TS_ITEMS],
-                                          uint32_t (&val)[TS_ITEMS], const TileBits& bits, int sh, int tn) {
+                                          uint32_t (&val)[TS_ITEMS], const uint32_t (&dg)[TS_ITEMS]) {
   const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
   const int p0 = wv * (TS_ITEMS * WAVE) + lane;
   auto& s_wh = lds.s_wh;
   constexpr int OR_XOR = 0xF0 | (0xCC ^ 0xAA);  // truth table of a | (b ^ c)
   for (int i = tid; i < TS_WAVES * 256; i += TS_THREADS) (&s_wh[0][0])[i] = 0;
   __syncthreads();
-  uint32_t rank[TS_ITEMS], dg[TS_ITEMS];
+  uint32_t rank[TS_ITEMS];
 #pragma unroll
   for (int j = 0; j < TS_ITEMS; ++j) {
-    dg[j] = p0 + j * WAVE < tn ? (uint32_t)(bits(key[j]) >> sh) & 255u : 255u;
     uint32_t mis_lo = 0, mis_hi = 0;  // lanes with another digit
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -126,7 +127,44 @@ __device__ __forceinline__ void tile_pass(TileSortLds& lds, DevState* ds, uint64
   }
 }
 
-constexpr int TS_RUN = 32;  // longest run of keys equal in the passes' bits that is ordered by counting
+// The pass by 8 bits of bits(key) >> sh.
+__device__ __forceinline__ void tile_key_pass(TileSortLds& lds, DevState* ds, uint64_t (&key)[TS_ITEMS],
+                                              uint32_t (&val)[TS_ITEMS], const TileBits& bits, int sh, int tn) {
+  const int p0 = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE) * (TS_ITEMS * WAVE) + lane_id();
+  uint32_t dg[TS_ITEMS];
+#pragma unroll
+  for (int j = 0; j < TS_ITEMS; ++j)
+    dg[j] = p0 + j * WAVE < tn ? (uint32_t)(bits(key[j]) >> sh) & 255u : 255u;
+  tile_pass(lds, ds, key, val, dg);
+}
+
+// The tile's keys and rows to LDS, where every thread reads its neighbours'.
+__device__ __forceinline__ void tile_store(TileSortLds& lds, const uint64_t (&key)[TS_ITEMS],
+                                           const uint32_t (&val)[TS_ITEMS], int p0) {
+  __syncthreads();  // (the passes' reads of the tile)
+#pragma unroll
+  for (int j = 0; j < TS_ITEMS; ++j) {
+    lds.s_key[p0 + j * WAVE] = key[j];
+    lds.s_val[p0 + j * WAVE] = val[j];
+  }
+  __syncthreads();
+}
+
+// The largest of each of the workgroup's values over its waves.
+template <int N>
+__device__ __forceinline__ void tile_max(TileSortLds& lds, uint64_t (&x)[N]) {
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const uint64_t m = wave_allmax_u64(x[i]);
+    if (lane == 0) lds.s_ext[i][wv] = m;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = wave_allmax_u64(lane < TS_WAVES ? lds.s_ext[i][lane] : 0ull);
+}
+
+constexpr int TS_RUN = 32;  // longest run of keys equal in the bits sorted so far that is ordered by counting
 
 __device__ __forceinline__ void tile_sort_body(const TileSortJobs& jobs, DevState* ds, TileSortLds& lds, uint32_t b) {
   int ji = 0;
@@ -163,14 +201,7 @@ __device__ __forceinline__ void tile_sort_body(const TileSortJobs& jobs, DevStat
     ext[2] = max(ext[2], ~tm);
     ext[3] = max(ext[3], tm);
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint64_t m = wave_allmax_u64(ext[i]);
-    if (lane == 0) lds.s_ext[i][wv] = m;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 4; ++i) ext[i] = wave_allmax_u64(lane < TS_WAVES ? lds.s_ext[i][lane] : 0ull);
+  tile_max(lds, ext);
   bits.seg0 = ~ext[0];
   bits.t0 = ~ext[2];
   bits.tb = bits_of(ext[3] - bits.t0);
@@ -180,48 +211,79 @@ __device__ __forceinline__ void tile_sort_body(const TileSortJobs& jobs, DevStat
   // another.  (With every digit sorted the launch took 25 us on 60k rows,
   // against 21.)
   int sh = rb > 16 ? rb - 16 : 0;
-  if (rb > 0) tile_pass(lds, ds, key, val, bits, sh, tn);
-  if (rb > 8) tile_pass(lds, ds, key, val, bits, sh + 8, tn);
-  __syncthreads();  // (the passes' reads of the tile)
-#pragma unroll
-  for (int j = 0; j < TS_ITEMS; ++j) {
-    s_key[p0 + j * WAVE] = key[j];
-    s_val[p0 + j * WAVE] = val[j];
-  }
-  __syncthreads();
-  if (sh > 0) {
-    // a run too long to count through: every digit, from the lowest
-    bool far = false;
+  if (rb > 0) tile_key_pass(lds, ds, key, val, bits, sh, tn);
+  if (rb > 8) tile_key_pass(lds, ds, key, val, bits, sh + 8, tn);
+  tile_store(lds, key, val, p0);
+  auto is_op = [&](uint64_t k) { return jb.contain && (k & 1) == 0; };
+  // Runs too long to count through.  Of keys equal in the top bits: every
+  // digit, from the lowest.  Of ops of equal key (starts on a coarse clock):
+  // their end times first, then every digit of the keys again.  (60k rows
+  // with starts on a 30 ms grid: 138 us a call, 126 with starts as they were;
+  // counting through runs of any length, each step a gather of two end times,
+  // 940.)
+  auto far = [&](bool ops) {
+    bool f = false;
 #pragma unroll
     for (int j = 0; j < TS_ITEMS; ++j) {
       const int p = p0 + j * WAVE + TS_RUN;
-      if (p < tn) far |= (bits(s_key[p]) >> sh) == (bits(key[j]) >> sh);
+      if (p < tn) f |= (bits(s_key[p]) >> sh) == (bits(key[j]) >> sh) && (!ops || is_op(key[j]));
     }
-    if (__syncthreads_or(far)) {
-      for (int d = 0; d < rb; d += 8) tile_pass(lds, ds, key, val, bits, d, tn);
-      sh = 0;
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < TS_ITEMS; ++j) {
-        s_key[p0 + j * WAVE] = key[j];
-        s_val[p0 + j * WAVE] = val[j];
-      }
-      __syncthreads();
-    }
+    return __syncthreads_or(f) != 0;
+  };
+  if (sh > 0 && far(false)) {
+    for (int d = 0; d < rb; d += 8) tile_key_pass(lds, ds, key, val, bits, d, tn);
+    sh = 0;
+    tile_store(lds, key, val, p0);
   }
+  bool done = sh == 0 && !jb.contain;  // nothing but equal keys is left, in row order
+  if (sh == 0 && jb.contain && far(true)) {
+    // end times down: from the tile's latest op on (launches keep their order)
+    auto end = [&](int j) { return (uint64_t)jobs.te[val[j]] ^ SIGN64; };
+    uint64_t te[2] = {0, 0};  // largest ~end, end of an op
+#pragma unroll
+    for (int j = 0; j < TS_ITEMS; ++j) {
+      if (p0 + j * WAVE >= tn || !is_op(key[j])) continue;
+      te[0] = max(te[0], ~end(j));
+      te[1] = max(te[1], end(j));
+    }
+    tile_max(lds, te);
+    const uint64_t last = te[1];
+    const int eb = bits_of(last - ~te[0]);
+    for (int d = 0; d < eb; d += 8) {
+      uint32_t dg[TS_ITEMS];
+#pragma unroll
+      for (int j = 0; j < TS_ITEMS; ++j)
+        dg[j] = p0 + j * WAVE >= tn ? 255u : is_op(key[j]) ? (uint32_t)((last - end(j)) >> d) & 255u : 0u;
+      tile_pass(lds, ds, key, val, dg);
+    }
+    for (int d = 0; d < rb; d += 8) tile_key_pass(lds, ds, key, val, bits, d, tn);
+    done = true;
+  }
+  if (done) {
+#pragma unroll
+    for (int j = 0; j < TS_ITEMS; ++j) {
+      const int p = p0 + j * WAVE;
+      if (p >= tn) continue;
+      jb.k[1][base + p] = key[j];
+      jb.v[1][base + p] = val[j];
+      if (p % TS_STEP == 0) jb.samples[tile * WAVE + p / TS_STEP] = key[j];
+    }
+    return;
+  }
+  // (a run of launches of equal key may be long: they keep their order)
 #pragma unroll
   for (int j = 0; j < TS_ITEMS; ++j) {
     const int p = p0 + j * WAVE;
     if (p >= tn) continue;
     const uint64_t k = key[j], h = bits(k) >> sh;
-    const bool op = jb.contain && (k & 1) == 0;
+    const bool op = is_op(k), counts = sh > 0 || op;
     int to = p;
-    for (int q = p - 1; q >= 0; --q) {  // those before that belong after
+    for (int q = p - 1; counts && q >= 0; --q) {  // those before that belong after
       const uint64_t o = s_key[q];
       if ((bits(o) >> sh) != h) break;
       to -= o > k || (op && o == k && jobs.te[s_val[q]] < jobs.te[val[j]]);
     }
-    for (int q = p + 1; q < tn; ++q) {  // those after that belong before
+    for (int q = p + 1; counts && q < tn; ++q) {  // those after that belong before
       const uint64_t o = s_key[q];
       if ((bits(o) >> sh) != h) break;
       to += o < k || (op && o == k && jobs.te[s_val[q]] > jobs.te[val[j]]);
@@ -323,11 +385,16 @@ __device__ __forceinline__ void tile_merge_body(const TileSortJobs& jobs, DevSta
         const bool later = t0 + u > tile;
         if (len[u] == 0 || x[u] != key || (later ? q[u] >= len[u] : q[u] == 0)) continue;
         const int tb = (t0 + u) * TS_TILE;
-        int a = q[u], e = q[u];
-        if (later)
-          while (e < len[u] && ks[tb + e] == key) ++e;
-        else
-          while (a > 0 && ks[tb + a - 1] == key) --a;
+        // the run's other end: steps doubled while the key is equal, then halved
+        const int from = later ? q[u] : q[u] - 1, room = later ? len[u] - 1 - from : from, dir = later ? 1 : -1;
+        int run = 0, step = 1;  // the key `run` steps on is equal
+        while (run + step <= room && ks[tb + from + dir * (run + step)] == key) {
+          run += step;
+          step *= 2;
+        }
+        for (step >>= 1; step > 0; step >>= 1)
+          if (run + step <= room && ks[tb + from + dir * (run + step)] == key) run += step;
+        int a = later ? from : from - run, e = later ? from + run + 1 : q[u];
         const int64_t own = jobs.te[val];
         while (a < e) {
           const int mid = (a + e) >> 1;

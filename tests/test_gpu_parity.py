@@ -392,6 +392,46 @@ def test_small_window_sorts(H, rows, times):
     check(H, cols, tr.params, f"{rows} rows, {times}")
 
 
+@pytest.mark.parametrize("rows,starts,ends", [(150, 1, 3), (4096, 1, 1 << 20), (4097, 1, 2), (9_000, 2, 1 << 38),
+                                              (40_000, 3, 7), (40_000, 40, 1 << 33), (131_072, 16, 1 << 20)])
+@pytest.mark.parametrize("ops", [0.9, 0.4])
+def test_small_window_equal_op_starts(H, rows, starts, ends, ops):
+    """Ops of one thread that start together, in runs longer than the tile sort
+    counts through: within a tile, whole tiles of one key, runs over several
+    tiles; end times of up to five digits, or few that many ops share (those in
+    row order); launches and kernels of the same starts among them."""
+    rng = np.random.default_rng(rows + starts)
+    w0, step = 7_000_000_000, (1 << 39) // starts
+    ts = w0 + rng.integers(0, starts, rows) * step
+    kind = np.where(rng.random(rows) < ops, 0, rng.integers(1, 3, rows))
+    te = ts + np.where(kind == 0, 1 + rng.integers(0, ends, rows), rng.integers(0, 50, rows))
+    cols = dict(ts=ts, te=te, corr=rng.integers(0, rows, rows), kind=kind, pid=np.zeros(rows), name=rng.integers(0, 4, rows),
+                lane=np.where(kind == 2, rng.integers(0, 3, rows), 0))
+    cols = {k: v.astype(np.uint8 if k == "kind" else np.int32 if k in ("pid", "lane", "name") else np.int64)
+            for k, v in cols.items()}
+    p = synth.empty_params(window_begin=w0, window_end=w0 + (1 << 40), n_streams=3, n_names=4, n_op_names=4)
+    check(H, cols, p, f"{rows} rows, {starts} starts, {ends} ends")
+
+
+def test_small_window_coarse_clock_time(H):
+    """Starts on a 30 ms grid: runs of hundreds and thousands of equal keys in
+    60,000 rows take less than 3.5 times the window with its own starts."""
+    tr = synth.config0()
+    ms = []
+    for grid in (1, 30_000_000):
+        cols = tr.columns()
+        w0 = tr.params["window_begin"]
+        for k in ("ts", "te"):
+            cols[k] = w0 + (cols[k] - w0) // grid * grid
+        n = len(cols["ts"])
+        an = H.Analyzer(tr.params, n)
+        d = H.device_columns(cols)
+        ev = H.events_struct(d)
+        assert an.run(ev, n) == 0
+        ms.append(_best_ms(lambda: an.run(ev, n)))
+    assert ms[1] < 3.5 * ms[0], ms
+
+
 @pytest.mark.parametrize("rows,times", [(140_000, "spread"), (140_000, "grid"), (1 << 18, "cluster"),
                                         (460_000, "cluster")])
 @pytest.mark.parametrize("P,S,T", [(8, 16, 4), (8, 16, 8), (300, 16, 16), (1000, 64, 16)])
