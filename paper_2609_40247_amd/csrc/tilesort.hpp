@@ -127,17 +127,6 @@ __device__ __forceinline__ void tile_pass(TileSortLds& lds, DevState* ds, uint64
   }
 }
 
-// The pass by 8 bits of bits(key) >> sh.
-__device__ __forceinline__ void tile_key_pass(TileSortLds& lds, DevState* ds, uint64_t (&key)[TS_ITEMS],
-                                              uint32_t (&val)[TS_ITEMS], const TileBits& bits, int sh, int tn) {
-  const int p0 = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE) * (TS_ITEMS * WAVE) + lane_id();
-  uint32_t dg[TS_ITEMS];
-#pragma unroll
-  for (int j = 0; j < TS_ITEMS; ++j)
-    dg[j] = p0 + j * WAVE < tn ? (uint32_t)(bits(key[j]) >> sh) & 255u : 255u;
-  tile_pass(lds, ds, key, val, dg);
-}
-
 // The tile's keys and rows to LDS, where every thread reads its neighbours'.
 __device__ __forceinline__ void tile_store(TileSortLds& lds, const uint64_t (&key)[TS_ITEMS],
                                            const uint32_t (&val)[TS_ITEMS], int p0) {
@@ -209,36 +198,47 @@ __device__ __forceinline__ void tile_sort_body(const TileSortJobs& jobs, DevStat
   // Two passes order the tile by the top 16 of these bits: of 4096 keys few
   // share them, and those that do count their way past one
   // another.  (With every digit sorted the launch took 25 us on 60k rows,
-  // against 21.)
-  int sh = rb > 16 ? rb - 16 : 0;
-  if (rb > 0) tile_key_pass(lds, ds, key, val, bits, sh, tn);
-  if (rb > 8) tile_key_pass(lds, ds, key, val, bits, sh + 8, tn);
-  tile_store(lds, key, val, p0);
+  // against 21.)  Runs too long to count through take further passes: of keys
+  // equal in the top bits, every digit from the lowest; of ops of equal key
+  // (starts on a coarse clock), their end times first, then the digits again.
+  // (60k rows with starts on a 30 ms grid: 138 us a call, 126 with starts as
+  // they were; counting through runs of any length, each step a gather of two
+  // end times, 940.)
   auto is_op = [&](uint64_t k) { return jb.contain && (k & 1) == 0; };
-  // Runs too long to count through.  Of keys equal in the top bits: every
-  // digit, from the lowest.  Of ops of equal key (starts on a coarse clock):
-  // their end times first, then every digit of the keys again.  (60k rows
-  // with starts on a 30 ms grid: 138 us a call, 126 with starts as they were;
-  // counting through runs of any length, each step a gather of two end times,
-  // 940.)
-  auto far = [&](bool ops) {
-    bool f = false;
+  auto end = [&](int j) { return (uint64_t)jobs.te[val[j]] ^ SIGN64; };
+  int sh = rb > 16 ? rb - 16 : 0;  // bits not sorted
+  bool ends = false, by_end = false;  // end times were sorted, are being sorted
+  uint64_t last = 0;                  // the latest of the tile's ops
+  for (int lo = sh, hi = rb;;) {
+    for (int d = lo; d < hi; d += 8) {
+      uint32_t dg[TS_ITEMS];
+#pragma unroll
+      for (int j = 0; j < TS_ITEMS; ++j) {
+        // end times down; launches keep their order
+        const uint64_t x = !by_end ? bits(key[j]) : is_op(key[j]) ? last - end(j) : 0;
+        dg[j] = p0 + j * WAVE < tn ? (uint32_t)(x >> d) & 255u : 255u;
+      }
+      tile_pass(lds, ds, key, val, dg);
+    }
+    lo = 0;
+    hi = rb;
+    if (by_end) {
+      by_end = false;
+      continue;
+    }
+    tile_store(lds, key, val, p0);
+    if (sh == 0 && (ends || !jb.contain)) break;
+    bool far = false;
 #pragma unroll
     for (int j = 0; j < TS_ITEMS; ++j) {
       const int p = p0 + j * WAVE + TS_RUN;
-      if (p < tn) f |= (bits(s_key[p]) >> sh) == (bits(key[j]) >> sh) && (!ops || is_op(key[j]));
+      if (p < tn) far |= (bits(s_key[p]) >> sh) == (bits(key[j]) >> sh) && (sh > 0 || is_op(key[j]));
     }
-    return __syncthreads_or(f) != 0;
-  };
-  if (sh > 0 && far(false)) {
-    for (int d = 0; d < rb; d += 8) tile_key_pass(lds, ds, key, val, bits, d, tn);
-    sh = 0;
-    tile_store(lds, key, val, p0);
-  }
-  bool done = sh == 0 && !jb.contain;  // nothing but equal keys is left, in row order
-  if (sh == 0 && jb.contain && far(true)) {
-    // end times down: from the tile's latest op on (launches keep their order)
-    auto end = [&](int j) { return (uint64_t)jobs.te[val[j]] ^ SIGN64; };
+    if (!__syncthreads_or(far)) break;
+    if (sh > 0) {
+      sh = 0;
+      continue;
+    }
     uint64_t te[2] = {0, 0};  // largest ~end, end of an op
 #pragma unroll
     for (int j = 0; j < TS_ITEMS; ++j) {
@@ -247,19 +247,11 @@ __device__ __forceinline__ void tile_sort_body(const TileSortJobs& jobs, DevStat
       te[1] = max(te[1], end(j));
     }
     tile_max(lds, te);
-    const uint64_t last = te[1];
-    const int eb = bits_of(last - ~te[0]);
-    for (int d = 0; d < eb; d += 8) {
-      uint32_t dg[TS_ITEMS];
-#pragma unroll
-      for (int j = 0; j < TS_ITEMS; ++j)
-        dg[j] = p0 + j * WAVE >= tn ? 255u : is_op(key[j]) ? (uint32_t)((last - end(j)) >> d) & 255u : 0u;
-      tile_pass(lds, ds, key, val, dg);
-    }
-    for (int d = 0; d < rb; d += 8) tile_key_pass(lds, ds, key, val, bits, d, tn);
-    done = true;
+    last = te[1];
+    hi = bits_of(last - ~te[0]);
+    ends = by_end = true;
   }
-  if (done) {
+  if (sh == 0 && (ends || !jb.contain)) {  // what is equal is in row order
 #pragma unroll
     for (int j = 0; j < TS_ITEMS; ++j) {
       const int p = p0 + j * WAVE;
