@@ -13,7 +13,8 @@ in HBM before timing.
 
 Prints one JSON line: events (all input rows) per second; the roofline of the
 dominant kernel (the radix digit passes) measured live with HIP events on the
-stream they run on; the whole call's algorithmic bytes over its wall time,
+stream they run on (none for a window that is launched level by level, whose
+calls run no such kernel); the whole call's algorithmic bytes over its wall time,
 warm and with a cold cache, beside the HBM traffic the committed rocprofv3
 counter profile measured over all analysis kernels; and the CPU oracle timed
 on this host.
@@ -34,7 +35,10 @@ METRIC = "trace events analyzed/sec (M ev/s) at 1 MI355X + achieved HBM GB/s % p
 HBM_PEAK_GBS = 8000.0
 ROOFLINE_STAGE = "sort"
 ROOFLINE_KERNEL = "k_radix_pass_packed"
-BYTES_PER_KEY_PASS = 16  # a digit pass reads and writes one 8-byte word (key above row)
+# A digit pass reads and writes one 8-byte word (key above row): every workload's keys, 36 to 40 bits, leave the
+# bits that do not fit beside the row to the refine pass.
+BYTES_PER_KEY_PASS = 16
+LEVEL_ROWS = 450_000  # windows up to this size are launched level by level unless a stage is timed (herschel.h)
 CSRC = os.path.join(ROOT, "paper_2609_40247_amd", "csrc")
 
 WORKLOADS = {
@@ -383,21 +387,22 @@ def main() -> int:
 
     # the roofline kernel: HIP events around the sort stage, recorded on the
     # stream its passes run on, over another K calls
-    stage_id = H.STAGES.index(ROOFLINE_STAGE)
-    pairs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(args.steps)]
     stream = torch.cuda.current_stream()
-    for a, b in pairs:  # create the events
-        a.record(stream)
-        b.record(stream)
-    torch.cuda.synchronize()
-    for a, b in pairs:
-        H.herschel_time_stage(stage_id, a, b)
-        run()
-    torch.cuda.synchronize()
-    H.herschel_time_stage(stage_id, None, None)
-    stage_ms = sum(a.elapsed_time(b) for a, b in pairs) / args.steps
-    # (of these calls: a small window is sorted without passes when no stage is timed)
-    units, launches = sort_units(H.herschel_sort_stats(an.params))
+    stage_ms = None
+    if n > LEVEL_ROWS:
+        stage_id = H.STAGES.index(ROOFLINE_STAGE)
+        pairs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(args.steps)]
+        for a, b in pairs:  # create the events
+            a.record(stream)
+            b.record(stream)
+        torch.cuda.synchronize()
+        for a, b in pairs:
+            H.herschel_time_stage(stage_id, a, b)
+            run()
+        torch.cuda.synchronize()
+        H.herschel_time_stage(stage_id, None, None)
+        stage_ms = sum(a.elapsed_time(b) for a, b in pairs) / args.steps
+        units, launches = sort_units(H.herschel_sort_stats(an.params))
 
     if args.stages:
         for sid, name in enumerate(H.STAGES):
@@ -414,12 +419,18 @@ def main() -> int:
             H.herschel_time_stage(sid, None, None)
             print(f"stage {name:14s} {tot / 5 * 1e3:9.1f} us", file=sys.stderr)
 
-    # per launch of the digit pass: the stage's bytes and time over its launches
-    alg = BYTES_PER_KEY_PASS * units / launches
-    launch_s = stage_ms * 1e-3 / launches
-    achieved = alg / launch_s / 1e9
     prof = profile_fields(args.workload + ("_waits" if args.waits else "") + ("_sol" if args.sol else "") +
                           ("_crit" if args.crit else ""))
+    roofline = None
+    if stage_ms is not None:  # per launch of the digit pass: the stage's bytes and time over its launches
+        alg = BYTES_PER_KEY_PASS * units / launches
+        launch_s = stage_ms * 1e-3 / launches
+        achieved = alg / launch_s / 1e9
+        roofline = {"kernel": ROOFLINE_KERNEL, "bound": "hbm", "achieved": round(achieved, 1),
+                    "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
+                    "traffic": None if prof is None else prof["radix_hbm_bytes_per_launch"],
+                    "algorithmic_bytes": round(alg), "launch_us": round(launch_s * 1e6, 2),
+                    "launches_per_step": launches, "key_passes_per_step": units}
     gaps = min(c["n_gaps_total"], an.gap_capacity)
     call_bytes = algorithmic_bytes(n, c, params, gaps)
     whole = {"algorithmic_bytes": call_bytes, "algorithmic_GBps": round(call_bytes / (ms * 1e-3) / 1e9, 1),
@@ -441,11 +452,7 @@ def main() -> int:
                    "outputs": "all" + (", with the idle coincidence by op name" if args.waits else "") +
                               (", with operator efficiency" if args.sol else "") +
                               (", with the critical path" if args.crit else "")},
-        "roofline": {"kernel": ROOFLINE_KERNEL, "bound": "hbm", "achieved": round(achieved, 1),
-                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": None if prof is None else prof["radix_hbm_bytes_per_launch"],
-                     "algorithmic_bytes": round(alg), "launch_us": round(launch_s * 1e6, 2),
-                     "launches_per_step": launches, "key_passes_per_step": units},
+        "roofline": roofline,
         "whole_call": whole,
     }
     if not args.no_cpu_baseline:
