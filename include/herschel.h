@@ -277,7 +277,8 @@ int herschel_workspace_size(int64_t n, const herschel_params *p, size_t *bytes);
  * HERSCHEL_* code.  On EEVENT only counters->first_invalid is defined.
  * The work is ordered on p->hip_stream (that of larger windows also runs on
  * two library streams that wait for, and are waited on by, that stream; up
- * to 450,000 rows it all runs on p->hip_stream); the call
+ * to 450,000 rows, 360,000 with HERSCHEL_OUT_CRIT and 280,000 with
+ * HERSCHEL_OUT_GRAPH unless replayed, it all runs on p->hip_stream); the call
  * returns once the device has finished all of it.  A call that launches
  * its kernels directly learns that from pinned host memory that its last
  * kernel writes (one small block per calling thread and device, allocated

@@ -244,10 +244,16 @@ static int crit_walk_max() {
 // Stage timing for benchmarks (herschel_time_stage).
 static int g_stage = -1;
 static hipEvent_t g_ev0 = nullptr, g_ev1 = nullptr;
-// Windows whose kernels are launched level by level: up to SMALL_ROWS rows,
-// unless a stage is being timed.
-static bool small_window(int64_t n) {
-  return g_stage < 0 && n <= SMALL_ROWS;
+// Windows whose kernels are launched level by level: up to SMALL_ROWS rows
+// (fewer with the outputs that gain by more streams, unless the call takes one
+// stream in any form), and with no stage being timed.
+static bool small_window(int64_t n, uint32_t flags, bool one_stream) {
+  int64_t most = SMALL_ROWS;
+  if (!one_stream && !(flags & HERSCHEL_REPLAY)) {
+    if (flags & HERSCHEL_OUT_CRIT) most = std::min(most, SMALL_ROWS_CRIT);
+    if (flags & HERSCHEL_OUT_GRAPH) most = std::min(most, SMALL_ROWS_GRAPH);
+  }
+  return g_stage < 0 && n <= most;
 }
 
 // ------------------------------------------------------------- the call
@@ -306,7 +312,7 @@ static int check_and_plan(Ctx& c, const herschel_events* ev, int64_t n, const he
   c.T = p->n_threads;
   c.NN = p->n_names;
   c.NOP = p->n_op_names;
-  c.small = small_window(n);
+  c.small = small_window(n, p->flags, false);
   c.contain = contain;
   c.overlap = overlap;
   c.waits = (p->flags & HERSCHEL_OUT_WAITS) != 0;
@@ -957,6 +963,7 @@ int herschel_trace_analyze_static(const herschel_events* ev, int64_t n, const he
   Ctx c;
   int code = check_and_plan(c, ev, n, p, out);
   if (code) return code;
+  c.small = small_window(n, p->flags, true);
   if (layout_workspace(c, nullptr) > (size_t)HERSCHEL_STATIC_SCRATCH_BYTES) return HERSCHEL_ETOOBIG;
   c.crit_deferred = c.crit;  // what marks long critical paths only if the call reports it needed
   {

@@ -229,11 +229,19 @@ constexpr int AG_CHAIN = 64;
 // stream; beyond, the three chains after the sorts run side by side on three
 // streams (us a call, level by level against three streams, traces of 4
 // streams: 150k rows 152 / 190, 300k 164 / 171, 450k 183 / 195, 600k 214 /
-// 200).  The smallest (up to TS_ROWS, TS_TILES tiles) also have their lists
+// 200; 446k rows without output flags 124 / 151, with the idle coincidence 231
+// / 251, eight processes 186 / 204, one stream 180 / 187, 16 streams 256 / 264,
+// shuffled rows with opaque ids 238 / 244, a batch of four 510 / 646).  The
+// critical path and the graph replay outputs lengthen the chain that a level
+// waits for, so their lines are lower: critical path 344k rows 252 / 256,
+// 389k 273 / 269, 446k 272 / 262, with the idle coincidence and operator
+// efficiency 302 / 308, 322 / 320 and 331 / 312; graph replays 258k rows 178 /
+// 192 (with the overlap 199 / 198), 310k 207 / 198 (245 / 205), 436k 247 / 210.
+// The smallest (up to TS_ROWS, TS_TILES tiles) also have their lists
 // sorted tile by tile (90k rows 129 against 154 us, 120k 144 against 154 in
 // delivery order and 152 against 156 in no order; with 64 tiles 240k rows
 // take 187 against 157).
-constexpr int64_t SMALL_ROWS = 450000;
+constexpr int64_t SMALL_ROWS = 450000, SMALL_ROWS_CRIT = 360000, SMALL_ROWS_GRAPH = 280000;
 constexpr int TS_TILE = 4096;
 constexpr int TS_TILES = 32;
 constexpr int64_t TS_ROWS = (int64_t)TS_TILE * TS_TILES;

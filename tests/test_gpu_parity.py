@@ -1525,6 +1525,23 @@ def test_graph_replay_workloads(H, shape):
     assert g["gn_count"].sum() > 0
 
 
+@pytest.mark.parametrize("rows,flags", [(360_000, 23), (360_001, 23), (280_000, 43), (280_001, 43), (280_001, 59)])
+def test_level_lines_of_optional_outputs(H, rows, flags):
+    """Windows on each side of the lines below which the critical path and the
+    graph replay outputs are launched level by level."""
+    if flags & H.OUT_GRAPH:
+        cols, p = synth.graph_replay_trace(n_steps=300, n_nodes=1000)
+        cols, p = synth.add_op_costs(cols, dict(p, flags=flags), 4)
+        cols = {k: v[:rows] for k, v in cols.items()}
+    else:
+        tr = synth.random_small(rows, n_rows=rows, window=rows * 6 // 5, n_procs=2, n_streams=4, n_threads=2,
+                                corr_range=rows // 7, flags=flags)
+        cols, p = tr.columns(), tr.params
+        cols["te"] = cols["ts"] + (cols["te"] - cols["ts"]) % 50
+    assert len(cols["ts"]) == rows
+    check(H, cols, p, f"{rows} rows, flags {flags}")
+
+
 def test_graph_null_outputs_and_errors(H):
     cols, p = synth.graph_replay_trace(n_steps=20, n_nodes=300)
     n = len(cols["ts"])

@@ -153,7 +153,7 @@ def test_idle_coincidence_is_captured_on_one_stream_only(fake, rows, captured):
     assert any(line.startswith("capture ") for line in log) == captured
 
 
-@pytest.mark.parametrize("rows", [400_000, 600_000, 20_000_000])
+@pytest.mark.parametrize("rows", [350_000, 600_000, 20_000_000])
 def test_inline_critical_path_launches(fake, rows):
     """A batch marks each window's critical path in line, with what a long path
     needs beyond the walk: launches with nothing to do in nearly every window.
@@ -169,3 +169,23 @@ def test_inline_critical_path_launches(fake, rows):
     rest = [k for k in launches(log) if "k_crit_" in k and not any(f"k_crit_{x}E" in k for x in needed)]
     rounds = (2 * rows - 1).bit_length() + 1
     assert code == 0 and len(rest) <= 2 * (rounds + (2 if rows <= 450_000 else 0)), rest[:40]
+
+
+@pytest.mark.parametrize("flags,most", [(0, 450_000), (3, 450_000), (7, 450_000), (1, 450_000), (17, 360_000), (23, 360_000),
+                                        (33, 280_000), (51, 280_000)])
+def test_level_by_level_lines(fake, flags, most):
+    """The largest windows that are launched level by level on the caller's
+    stream, by their outputs (each line where three streams begin to win); with
+    replay asked for and through the entry point that takes one stream, the same
+    for all outputs."""
+    res = child(fake, f"""
+        device()
+        for n in ({most}, {most} + 1):
+            p = params(flags={flags}, n_graph_nodes=100)
+            out.append((H.herschel_trace_analyze(EV, n, p, outputs()), log()))
+        out.append((H.herschel_trace_analyze(EV, 450_000, params(flags={flags} | H.REPLAY, n_graph_nodes=100), outputs()), log()))
+        out.append((H.herschel_trace_analyze_static(EV, 150_000, params(flags={flags}, n_graph_nodes=100), outputs()), log()))
+    """)
+    small = [any("k_level" in k for k in launches(log)) for _, log in res]
+    assert all(code == 0 for code, _ in res) and small == [True, False, True, True], small
+    assert not any(line.startswith(("record", "wait")) for line in res[0][1])
